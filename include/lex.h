@@ -74,7 +74,7 @@ typedef struct {
 typedef struct {
   uint64_t ntokens;      /* tokens written; if status == LEX_EOVERFLOW, tokens required     */
   uint64_t error_offset; /* con(w); == n iff the input is completely tokenizable             */
-  int32_t status;        /* LEX_OK or LEX_EOVERFLOW                                          */
+  int32_t status;        /* LEX_OK or LEX_EOVERFLOW (LEX_EDEVICE: a workgroup never answered) */
   uint32_t nslices;      /* non-empty slices the plan produced (1 for a serial scan)         */
 } lex_result;
 
@@ -149,23 +149,23 @@ int lex_tables(const lex_dfa *dfa, int mode, uint32_t *table, size_t table_entri
  * walk, scan, emit walk); 2 = fused (each lane finds its own cut, no bitmap; count walk,
  * scan and emit walk as separate launches); 3 = fused in one pass (windowed scans only,
  * else as 2): 256-lane workgroups take their lanes in order, count-walk them, find their
- * first output slot by a look-back over the earlier workgroups' published totals, and
- * emit, all in one launch; 0 = default: 3 where it applies, else 2.  block_threads:
+ * first output slot by a look-back over the earlier workgroups' published totals, emit and
+ * write the result, all in one launch; 0 = default: 3 where it applies, else 2.  block_threads:
  * threads per walk workgroup, 256, 512 or 1024 (0 = the largest whose LDS fits; one pass
  * uses 256 and a default path given another value takes path 2).  emit: 0 = default,
  * 1 = lane emit only.  By default a scan of an automaton with at most 256 rows uses the
  * windowed emit: the count
  * walk records checkpoints every 64 bytes and the emit walk runs one thread per 64-byte
- * sub-slice; a scan with a halted slice or a slice of 2^24 bytes or more falls back to the
- * lane emit (one thread per slice) on the device, and so does a scan of a non-monotone
+ * sub-slice, up to the scan's halt if it has one; a scan with a slice of 2^24 bytes or more
+ * writes its tokens with one thread per slice on the device, and so does a scan of a non-monotone
  * automaton (a live edge from an accepting to a non-accepting state) in which some slice
  * fell back to an earlier accepting position.  One pass needs a monotone automaton and
  * certified cuts.  All write the same outputs.  events:
  * optional array of LEX_NPHASES + 1 hipEvent_t (passed as void*, created by the caller)
  * recorded on the scan's stream at the phase boundaries: [0] start, [1] after planning
  * (steps a, b), [2] after the count walk (c), [3] after the scan (d), [4] after the emit
- * walk (e).  In one pass, [1] follows the reset of the look-back state, [2] the one-pass
- * launch (planning, count walk and windowed emit) and [4] the lane emit's fallback. */
+ * walk (e).  In one pass, [1] follows the reset of the look-back state and [2] to [4] the
+ * one-pass launch (planning, count walk, scan and emit). */
 enum { LEX_NPHASES = 4 };
 enum { LEX_EMIT_DEFAULT = 0, LEX_EMIT_LANE = 1 };
 typedef struct {

@@ -60,6 +60,10 @@ struct Plan {
   // of the decoupled look-back, and the counter that hands the workgroups out in order.
   uint64_t *chunk_st;      // nblocks
   uint32_t *chunk_ctr;
+  // Windowed scans in separate launches (in chunk_st's place): per workgroup of lanes, the
+  // start of the failed token of its first halted lane.
+  uint32_t *blk_tok;
+  int pipelined;           // slices are [cuts[j], cuts[j + 1]) (pipeline and hybrid plans)
   // Hybrid plan (a refused set split speculatively; lane_bytes is the speculative lane):
   // per lane its cut, last restart and head/tail token starts, and the fall-back flag.
   int hybrid;
