@@ -140,14 +140,15 @@ struct BatchTables {
   uint32_t ninst;
   BatchInstHost inst[kBatchMaxInst];
 };
-// Workspace of a batch of ndocs documents over nbytes bytes with lane target lane_bytes.
-size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes);
+// Workspace of a batch of ndocs documents over nbytes bytes with lane target lane_bytes (chosen:
+// by the caller; a default lane may be walked in finer ones, its slices counted as planned).
+size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen);
 // LDS of the batched lane-emit workgroup (the count walk needs less): 0 if it does not fit.
 // (The windowed emit takes as many waves as fit beside the table, or stands down.)
 size_t batch_emit_lds_bytes(int nrows, uint32_t ninst);
 // docs: device array of 16-byte lex_doc; res: device array of 32-byte lex_doc_result.
 hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbytes, const void *docs, uint32_t ndocs,
-                     uint32_t lane_bytes, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap, void *res,
-                     ResultDev *total, void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t const *ev);
+                     uint32_t lane_bytes, bool chosen, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap,
+                     void *res, ResultDev *total, void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t const *ev);
 
 }  // namespace lexk

@@ -2074,10 +2074,9 @@ struct DocResDev {  // mirrors lex_doc_result
   uint32_t nslices;
 };
 
-// meta words: work queues (count, lane emit; kQWin is reset but no kernel takes from it),
-// lane / speculative-lane / tile totals, a stopped batch, no windowed emit for this batch,
+// meta words: work queues (count, lane emit), lane / speculative-lane / tile totals, a stopped batch, no windowed emit for this batch,
 // some document for the lane emit
-enum { kQCount = 0, kQEmit = 1, kNLanes = 2, kBad = 3, kNSpec = 4, kQWin = 5, kNTiles = 6, kNoWin = 7,
+enum { kQCount = 0, kQEmit = 1, kNLanes = 2, kBad = 3, kNSpec = 4, kNTiles = 6, kNoWin = 7,
        kAnyLane = 8, kBatchMeta = 16 };
 
 struct BatchArgs {
@@ -2089,11 +2088,13 @@ struct BatchArgs {
   const uint8_t *bytes;
   uint64_t nbytes;
   const DocDev *docs;
-  uint32_t ndocs, lane_bytes, max_lanes;
+  // lane_bytes: the plan's lane, which slices are counted by; fine_bytes: the lane that is walked
+  // (lane_bytes over a power of two: a small batch has too few lanes of its own to fill the chip)
+  uint32_t ndocs, lane_bytes, fine_bytes, max_lanes;
   uint32_t *meta;  // kBatchMeta words: queues, lane count
   uint64_t *part;  // kDocGroups x kPartWords: per-group sums of the planning and result kernels
   uint32_t *lanes_of, *lane_base, *lane_doc, *cuts, *ends, *counts, *halted, *lane_pre, *doc_halt;
-  uint32_t *doc_ntok, *doc_nsl;
+  uint32_t *doc_ntok, *doc_nsl, *doc_err;
   // hybrid plan: per document the first speculative lane's index and the fall-back flag;
   // per speculative lane its document, cut, last restart, and head then tail token starts
   uint32_t spec_bytes, max_spec;
@@ -2179,14 +2180,14 @@ __device__ __forceinline__ bool spec_split(const BatchArgs &a, uint32_t rm, cons
 __device__ __forceinline__ bool one_lane(const BatchArgs &a, uint32_t rm, const DocDev &d) {
   // (an unknown instance stops the batch)
   return !spec_split(a, rm, d) &&
-         (d.length <= a.lane_bytes || (d.flags & 1) || d.inst >= a.ninst || ((rm >> d.inst) & 1));
+         (d.length <= a.fine_bytes || (d.flags & 1) || d.inst >= a.ninst || ((rm >> d.inst) & 1));
 }
 
 __device__ __forceinline__ uint32_t ceil_div(uint32_t x, uint32_t y) { return x / y + (x % y != 0); }
 
 __device__ __forceinline__ uint32_t doc_lanes(const BatchArgs &a, uint32_t rm, const DocDev &d) {
   if (spec_split(a, rm, d)) return ceil_div(d.length, a.spec_bytes);
-  return one_lane(a, rm, d) ? 1 : ceil_div(d.length, a.lane_bytes);
+  return one_lane(a, rm, d) ? 1 : ceil_div(d.length, a.fine_bytes);
 }
 
 // The planning and result kernels (k_bplan_*, k_bscan_*) split the document table into at
@@ -2221,10 +2222,12 @@ __device__ __forceinline__ uint64_t wave_incl64(uint64_t v, uint32_t lane) {
   return v;
 }
 
-// Sums of Q values over the workgroup (256 threads); red: Q x 4 words of LDS.
+constexpr uint32_t kRedWaves = 16;  // waves of the largest workgroup that sums (LDS words per value)
+
+// Sums of Q values over the workgroup; red: Q x kRedWaves words of LDS.
 template <int Q>
-__device__ __forceinline__ void block_sum(uint64_t (&v)[Q], uint64_t (*red)[4]) {
-  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+__device__ __forceinline__ void block_sum(uint64_t (&v)[Q], uint64_t (*red)[kRedWaves]) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
   for (int q = 0; q < Q; ++q) v[q] = wave_sum64(v[q]);
   if (lane == 0)
@@ -2232,14 +2235,17 @@ __device__ __forceinline__ void block_sum(uint64_t (&v)[Q], uint64_t (*red)[4]) 
     for (int q = 0; q < Q; ++q) red[q][wid] = v[q];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < Q; ++q) v[q] = red[q][0] + red[q][1] + red[q][2] + red[q][3];
+  for (int q = 0; q < Q; ++q) {
+    v[q] = 0;
+    for (uint32_t w = 0; w < nw; ++w) v[q] += red[q][w];
+  }
   __syncthreads();
 }
 
-// Inclusive scan of Q values over the workgroup (256 threads), and their totals.
+// Inclusive scan of Q values over the workgroup, and their totals.
 template <int Q>
-__device__ __forceinline__ void block_incl(uint64_t (&v)[Q], uint64_t (&tot)[Q], uint64_t (*red)[4]) {
-  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+__device__ __forceinline__ void block_incl(uint64_t (&v)[Q], uint64_t (&tot)[Q], uint64_t (*red)[kRedWaves]) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
   for (int q = 0; q < Q; ++q) v[q] = wave_incl64(v[q], lane);
   if (lane == 63)
@@ -2249,7 +2255,7 @@ __device__ __forceinline__ void block_incl(uint64_t (&v)[Q], uint64_t (&tot)[Q],
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     uint64_t pre = 0, t = 0;
-    for (uint32_t w = 0; w < 4; ++w) {
+    for (uint32_t w = 0; w < nw; ++w) {
       pre += w < wid ? red[q][w] : 0;
       t += red[q][w];
     }
@@ -2263,7 +2269,7 @@ __device__ __forceinline__ void block_incl(uint64_t (&v)[Q], uint64_t (&tot)[Q],
 // groups (tot).
 template <int Q>
 __device__ __forceinline__ void group_prefix(const uint64_t *part, uint32_t q0, uint64_t (&pre)[Q],
-                                             uint64_t (&tot)[Q], uint64_t (*red)[4]) {
+                                             uint64_t (&tot)[Q], uint64_t (*red)[kRedWaves]) {
   const uint32_t t = threadIdx.x;
   uint64_t v[2 * Q];
 #pragma unroll
@@ -2281,22 +2287,20 @@ __device__ __forceinline__ void group_prefix(const uint64_t *part, uint32_t q0, 
 }
 
 // Planning, first half: lanes per document, each group's lane, speculative-lane and tile
-// sums and whether it holds a bad record; the queues reset.  The document table is the
+// sums (v) and whether it holds a bad record; the queues reset.  The document table is the
 // caller's device data: a document outside the bytes, an unknown instance or flag, or more
 // lanes than the workspace holds stops the batch.
-__global__ void __launch_bounds__(256) k_bplan_a(BatchArgs a) {
-  __shared__ uint64_t red[5][4];
+// v: single-lane long documents, other lanes, speculative lanes, tiles, bad
+__device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[5],
+                                          uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.meta[kQCount] = 0;
     a.meta[kQEmit] = 0;
-    a.meta[kQWin] = 0;
     a.meta[kAnyLane] = 0;
   }
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  uint32_t lo, hi;
-  group_range(a.ndocs, lo, hi);
-  uint64_t v[5] = {0, 0, 0, 0, 0};  // single-lane long documents, other lanes, speculative lanes, tiles, bad
+  for (int q = 0; q < 5; ++q) v[q] = 0;
   for (uint32_t d = lo + threadIdx.x; d < hi; d += blockDim.x) {
     const DocDev x = a.docs[d];
     const bool fits = x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
@@ -2304,34 +2308,29 @@ __global__ void __launch_bounds__(256) k_bplan_a(BatchArgs a) {
     const uint32_t nl = doc_lanes(a, rm, x);
     a.lanes_of[d] = nl;
     a.spec_fail[d] = 0;
-    const bool first = nl == 1 && x.length > a.lane_bytes;
+    const bool first = nl == 1 && x.length > a.fine_bytes;
     v[0] += first ? nl : 0;
     v[1] += first ? 0 : nl;
     if (spec_split(a, rm, x)) v[2] += nl;
     if (fits) v[3] += doc_tiles(base + x.offset, x.length);
   }
   block_sum<5>(v, red);
-  if (threadIdx.x < 5) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
 }
 
 // Planning, second half: lane numbering (long single-lane documents first, then the rest,
-// each in document order), speculative-lane and tile numbering; the first group writes the
-// totals and the stop flags.
-__global__ void __launch_bounds__(256) k_bplan_b(BatchArgs a) {
-  __shared__ uint64_t red[10][4];
+// each in document order), speculative-lane and tile numbering, from the sums of the earlier
+// groups (pre) and of all (tot); the first group writes the totals and the stop flags.
+__device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uint32_t hi, const uint64_t (&pre)[5],
+                                            const uint64_t (&tot)[5], uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  uint64_t pre[5], tot[5];
-  group_prefix<5>(a.part, 0, pre, tot, red);
   uint64_t r[4] = {pre[0], tot[0] + pre[1], pre[2], pre[3]};  // 64-bit: a hostile table may ask for 2^32 lanes
-  uint32_t lo, hi;
-  group_range(a.ndocs, lo, hi);
   for (uint32_t d0 = lo; d0 < hi; d0 += blockDim.x) {  // workgroup-uniform: the scans see every thread
     const uint32_t d = d0 + threadIdx.x;
     const bool in = d < hi;
     const DocDev x = a.docs[in ? d : lo];
-    const uint32_t nl = in ? a.lanes_of[d] : 0;
-    const bool first = nl == 1 && x.length > a.lane_bytes;
+    const uint32_t nl = in ? doc_lanes(a, rm, x) : 0;
+    const bool first = nl == 1 && x.length > a.fine_bytes;
     const bool fits = in && x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
     uint64_t v[4] = {first ? nl : 0, first ? 0 : nl, in && spec_split(a, rm, x) ? nl : 0,
                      fits ? doc_tiles(base + x.offset, x.length) : 0};
@@ -2362,9 +2361,8 @@ __global__ void __launch_bounds__(256) k_bplan_b(BatchArgs a) {
 }
 
 // A wave per document: the lane -> document map.
-__global__ void __launch_bounds__(256) k_bmap(BatchArgs a) {
+__device__ __forceinline__ void map_docs(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nwaves = (gridDim.x * blockDim.x) >> 6;
   if (a.meta[kBad]) return;
   const bool win = !a.meta[kNoWin];
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
@@ -2379,6 +2377,40 @@ __global__ void __launch_bounds__(256) k_bmap(BatchArgs a) {
       for (uint32_t k = lane; k < nt; k += 64) a.tile_doc[tb + k] = d;
     }
   }
+}
+
+__global__ void __launch_bounds__(256) k_bplan_a(BatchArgs a) {
+  __shared__ uint64_t red[5][kRedWaves];
+  uint32_t lo, hi;
+  group_range(a.ndocs, lo, hi);
+  uint64_t v[5];
+  plan_sums(a, lo, hi, v, red);
+  if (threadIdx.x < 5) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
+}
+
+__global__ void __launch_bounds__(256) k_bplan_b(BatchArgs a) {
+  __shared__ uint64_t red[10][kRedWaves];
+  uint64_t pre[5], tot[5];
+  group_prefix<5>(a.part, 0, pre, tot, red);
+  uint32_t lo, hi;
+  group_range(a.ndocs, lo, hi);
+  plan_number(a, lo, hi, pre, tot, red);
+}
+
+__global__ void __launch_bounds__(256) k_bmap(BatchArgs a) {
+  map_docs(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+}
+
+// A small batch (one_plan) in one launch of one workgroup: a launch costs 4-5 us here, more
+// than the planning of a few hundred documents.
+__global__ void __launch_bounds__(1024) k_bplan_one(BatchArgs a) {
+  __shared__ uint64_t red[5][kRedWaves];
+  uint64_t tot[5];
+  const uint64_t pre[5] = {0, 0, 0, 0, 0};
+  plan_sums(a, 0, a.ndocs, tot, red);
+  plan_number(a, 0, a.ndocs, pre, tot, red);
+  __syncthreads();
+  map_docs(a, threadIdx.x >> 6, blockDim.x >> 6);
 }
 
 // Speculative walk of [b, end) (hybrid plan): from the start row as if a token began at b,
@@ -2640,16 +2672,19 @@ __device__ __forceinline__ uint32_t next_tile(uint32_t *q) {
 // launch of their own), then the lanes of every document the hybrid plan does not split,
 // which keep the chip busy meanwhile.  The split documents are counted after the cuts
 // (k_bsplit).
+template <int LINE>
 __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
   const BatchLds l = batch_stage(a);
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t nlanes = a.meta[kNLanes], nspec = a.meta[kNSpec];
   const uint32_t nst = (nspec + 63) / 64;  // speculative tiles first
   const bool ck_on = !a.meta[kNoWin];
+  const uint32_t rm = refused_mask(a);
   // every wave's first tile is fixed (all waves taking it from the queue at once would
   // queue on its atomic counter); later ones come from the queue, past the fixed ones
   const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6, gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  for (uint32_t tile = gw;; tile = next_tile(&a.meta[kQCount]) + nwaves) {
+  const bool queued = nst + (nlanes + 63) / 64 > nwaves;
+  for (uint32_t tile = gw;; tile = queued ? next_tile(&a.meta[kQCount]) + nwaves : kNone) {
     if (tile < nst) {  // wave-uniform
       const uint32_t i = tile * 64 + lane;
       if (i < nspec) spec_lane(a, l, i);
@@ -2659,7 +2694,7 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
     if ((uint64_t)t * 64 >= nlanes) break;  // wave-uniform exit
     const uint32_t j = t * 64 + lane;
     const bool valid = j < nlanes;
-    uint32_t d = 0, jj = 0, nl = 1, start = kNone;
+    uint32_t d = kNone, jj = 0, nl = 1, start = kNone;
     DocDev doc{0, 0, 0, 0};
     if (valid) {
       d = a.lane_doc[j];
@@ -2670,52 +2705,58 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
     const BatchInst &in = a.inst[valid ? doc.inst : 0];
     const uint8_t *src = a.bytes + doc.offset;
     const uint8_t *lut = l.luts + 256 * (valid ? doc.inst : 0);
-    const bool spec = valid && spec_split(a, refused_mask(a), doc);
-    if (valid && !spec) {
-      if (jj == 0) start = 0;
-      else start = search_cert(src, doc.length, in.ca, lut, jj * a.lane_bytes, a.lane_bytes, kNone);
+    const bool mine = valid && !spec_split(a, rm, doc);
+    if (mine) {
+      if (jj) start = search_cert(src, doc.length, in.ca, lut, jj * a.fine_bytes, a.fine_bytes, kNone);
+      else if (doc.length) start = 0;
     }
-    // the next lane's start, when that lane is this document's and this tile's
-    const uint32_t nstart = (uint32_t)__shfl_down((int)start, 1);
-    if (!valid || spec) continue;
-    const bool same = lane < 63 && jj + 1 < nl;
-    uint32_t s, e;
+    // a slice ends where the document's next non-empty lane's starts: in this tile, or past it
+    // when the document's lanes run on
+    const uint64_t ne = __ballot(start != kNone);
+    const uint64_t after = ne & ~((2ull << lane) - 1);
+    const int f = after ? __ffsll((unsigned long long)after) - 1 : 0;
+    const uint32_t fs = (uint32_t)__shfl((int)start, f), fd = (uint32_t)__shfl((int)d, f);
+    uint32_t s = 0, e = 0;
     if (start == kNone) {
-      s = e = min(jj * a.lane_bytes, doc.length);
+      s = e = min(jj * a.fine_bytes, doc.length);
     } else {
       s = start;
-      if (jj + 1 == nl) e = doc.length;
-      else if (same && nstart != kNone) e = nstart;
-      else {
-        const uint32_t x1 = (jj + 1) * a.lane_bytes;
+      if (after && fd == d) {
+        e = fs;
+      } else if (jj + (64 - lane) >= nl) {
+        e = doc.length;
+      } else {
+        const uint32_t x1 = (jj + (64 - lane)) * a.fine_bytes;
         e = search_cert(src, doc.length, in.ca, lut, x1, doc.length - x1, doc.length);
       }
     }
-    a.cuts[j] = s;
-    a.ends[j] = e;
+    if (mine) {
+      a.cuts[j] = s;
+      a.ends[j] = e;
+    }
     const Tables tb{l.T, l.info, l.kind, in.sink, in.fail, in.start};
     LaneState L;
-    L.cnt = 0;
-    Ring r{};
     // checkpoints for the windowed emit: main slots by the window's place in the lane's
     // nominal range, else the document's overflow region (its 64 windows per tile)
     CkSink ck{};
-    if (ck_on) {
+    if (ck_on && mine) {
       ck.base = reinterpret_cast<uintptr_t>(src);
       ck.main = a.ck_main;
       ck.over = a.ck_over + (size_t)a.tile_base[d] * 64;
       ck.nlanes = a.max_lanes;
       ck.kslots = a.kslots;
       ck.j = j;
-      ck.jl = jj * a.lane_bytes;
+      ck.jl = jj * a.fine_bytes;
       ck.mis0 = (uint32_t)(ck.base & (kWin - 1));
     }
-    const bool halted = in.mono ? walk<false, true, false, true>(L, r, tb, src, doc.length, s, e, ck)
-                                : walk<false, false, false, true>(L, r, tb, src, doc.length, s, e, ck);
-    a.counts[j] = L.cnt;
-    // bit 0: the slice halted; bit 1: no windowed emit for its document (a fallback
-    // re-scanned positions the checkpoints describe, or counts overflow 24 bits)
-    a.halted[j] = (halted ? 1u : 0u) | ((L.fb || e - s >= (1u << 24)) ? 2u : 0u);
+    const bool halted = walk_wave<LINE, true, true>(L, tb, src, doc.length, s, e, doc.length, start != kNone, ck);
+    if (mine) {
+      a.counts[j] = L.cnt;
+      // bit 0: the slice halted; bit 1: no windowed emit for its document (a fallback
+      // re-scanned positions the checkpoints describe, or counts overflow 24 bits)
+      a.halted[j] = (halted ? 1u : 0u) | ((L.fb || e - s >= (1u << 24)) ? 2u : 0u);
+      if (halted) a.lane_pre[j] = L.tok;  // the failed token's start, for the document pass
+    }
   }
 }
 
@@ -2794,25 +2835,18 @@ __global__ void __launch_bounds__(256) k_bsplit(BatchArgs a) {
     const uint8_t *src = a.bytes + doc.offset;
     const Tables tb{l.T, l.info, l.kind, in.sink, in.fail, in.start};
     LaneState L;
-    L.cnt = 0;
-    L.fb = 0;
-    Ring r{};
-    bool halted = false;
-    if (valid) {
-      CkSink ck{};
-      if (ck_on) {
-        ck.base = reinterpret_cast<uintptr_t>(src);
-        ck.main = a.ck_main;
-        ck.over = a.ck_over + (size_t)a.tile_base[d] * 64;
-        ck.nlanes = a.max_lanes;
-        ck.kslots = a.kslots;
-        ck.j = j;
-        ck.jl = k * a.spec_bytes;
-        ck.mis0 = (uint32_t)(ck.base & (kWin - 1));
-      }
-      halted = in.mono ? walk<false, true, false, true>(L, r, tb, src, doc.length, p, pe, ck)
-                       : walk<false, false, false, true>(L, r, tb, src, doc.length, p, pe, ck);
+    CkSink ck{};
+    if (ck_on && valid) {
+      ck.base = reinterpret_cast<uintptr_t>(src);
+      ck.main = a.ck_main;
+      ck.over = a.ck_over + (size_t)a.tile_base[d] * 64;
+      ck.nlanes = a.max_lanes;
+      ck.kslots = a.kslots;
+      ck.j = j;
+      ck.jl = k * a.spec_bytes;
+      ck.mis0 = (uint32_t)(ck.base & (kWin - 1));
     }
+    const bool halted = walk_wave<64, true, true>(L, tb, src, doc.length, p, pe, pe, valid, ck);
     // the lane's count: its parts' up to the first that halted; inclusive prefixes in the group
     uint32_t pre = valid ? L.cnt : 0;
     for (uint32_t dd = 1; dd < kParts; dd <<= 1) {
@@ -2827,9 +2861,11 @@ __global__ void __launch_bounds__(256) k_bsplit(BatchArgs a) {
                    pre2 = (uint32_t)__shfl((int)pre, g0 + 2);
     const uint32_t p1 = (uint32_t)__shfl((int)p, g0 + 1), p2 = (uint32_t)__shfl((int)p, g0 + 2),
                    p3 = (uint32_t)__shfl((int)p, g0 + 3);
+    const uint32_t he = (uint32_t)__shfl((int)pe, g0 + qh);
+    if (valid && gh && q == qh) a.lane_pre[j] = L.tok;  // the failed token's start, for the document pass
     if (valid && q == 0) {
       a.cuts[j] = s;
-      a.ends[j] = e;
+      a.ends[j] = gh ? he : e;  // (nothing past a halted part is the scan's)
       a.counts[j] = tot;
       a.halted[j] = (gh ? 1u : 0u) | ((gf || e - s >= (1u << 24)) ? 2u : 0u);
       a.spec_part[i] = make_uint4(p1, p2, p3, 0);
@@ -2838,14 +2874,15 @@ __global__ void __launch_bounds__(256) k_bsplit(BatchArgs a) {
   }
 }
 
-// A wave per document: its first halted lane, the token count up to and including it,
-// in-document prefixes of the lane counts, non-empty slices.
-__global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
-  if (a.meta[kBad]) return;
+// A wave per document: its first halted lane and the start of its failed token, the token
+// count up to and including it, in-document prefixes of the lane counts, non-empty slices.
+// Slices are the plan's: where the walked lanes are finer, a plan lane has one when any of its
+// walked lanes has.  True if some document of this wave's takes the lane emit.
+__device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nwaves = (gridDim.x * blockDim.x) >> 6;
   const bool win = !a.meta[kNoWin];
-  bool any_lane = false;  // some document of this wave's takes the lane emit
+  const uint32_t rm = refused_mask(a);
+  bool any_lane = false;
   // the next document's lane range and the next chunk's lanes load while the current ones
   // are scanned (a document of thousands of lanes would otherwise wait on every chunk)
   uint32_t n_lb = 0, n_nl = 1;
@@ -2859,7 +2896,12 @@ __global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
       n_lb = a.lane_base[d + nwaves];
       n_nl = a.lanes_of[d + nwaves];
     }
-    uint32_t run = 0, nsl = 0, halt = kNone;
+    const DocDev doc = a.docs[d];
+    // walked lanes per plan lane (a power of two up to 64, so that 64-lane chunks hold whole ones)
+    const bool split = spec_split(a, rm, doc);
+    const uint32_t ratio = split ? 1 : a.lane_bytes / a.fine_bytes;
+    const uint64_t heads = ratio < 64 ? ~0ull / ((1ull << ratio) - 1) : 1;  // the first bit of every `ratio`
+    uint32_t run = 0, nsl = 0, halt = kNone, err = doc.length;
     bool nowin = !win;
     int32_t zrun = -1;  // last non-empty lane of the earlier chunks
     // lanes past the document's last reload that lane (any defined value does)
@@ -2891,74 +2933,59 @@ __global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
           z = max(z, zz);
         }
       }
+      const unsigned long long hb = __ballot(h), nb = __ballot(ne);
+      if (hb) err = a.lane_pre[lb + c + __ffsll(hb) - 1];  // wave-uniform
       if (ok) {
         a.lane_pre[j] = run + incl - cnt;
         if (win) a.lnz[j] = (uint32_t)z;
       }
       nowin = nowin || __any(hf & 2);
       zrun = __shfl(z, 63);
-      const unsigned long long hb = __ballot(h), nb = __ballot(ne);
+      unsigned long long live = nb;
+      const int f = hb ? __ffsll(hb) - 1 : 63;
+      live &= (2ull << f) - 1;
+      for (uint32_t r = 1; r < ratio; r <<= 1) live |= live >> r;
+      nsl += __popcll(live & heads);
+      run += (uint32_t)__shfl((int)incl, f);
       if (hb) {  // wave-uniform
-        const int f = __ffsll(hb) - 1;
-        run += (uint32_t)__shfl((int)incl, f);
-        nsl += __popcll(nb & ((2ull << f) - 1));
         halt = lb + c + f;
+        // the halted slice may run past this chunk's lanes (empty ones, from there to its end):
+        // the windows in it find it through them
+        const uint32_t end = (uint32_t)__shfl((int)en0, f);  // > 0: a halted slice is not empty
+        const uint32_t far = min(nl - 1, (end - 1) / (split ? a.spec_bytes : a.fine_bytes));
+        for (uint32_t k = c + 64 + lane; win && k <= far; k += 64) a.lnz[lb + k] = halt;
         break;
       }
-      run += (uint32_t)__shfl((int)incl, 63);
-      nsl += __popcll(nb);
     }
     if (lane == 0) {
       a.doc_ntok[d] = run;
       a.doc_halt[d] = halt;
+      a.doc_err[d] = err;
       a.doc_nsl[d] = nsl;
-      // a halted document, a fallback or a long slice: the lane emit writes it
-      const bool w = !nowin && halt == kNone;
-      a.doc_win[d] = w;
-      any_lane |= !w;
+      a.doc_win[d] = !nowin;  // a fallback or a long slice: the lane emit writes it
+      any_lane |= nowin;
     }
   }
-  if (lane == 0 && any_lane) a.meta[kAnyLane] = 1;  // every writer stores the same value
+  return any_lane;
 }
 
-// Results, first half: each group's token, halted-document and slice sums.
-__global__ void __launch_bounds__(256) k_bscan_a(BatchArgs a) {
-  __shared__ uint64_t red[3][4];
-  if (a.meta[kBad]) return;  // uniform: no barrier follows
-  uint32_t lo, hi;
-  group_range(a.ndocs, lo, hi);
-  uint64_t v[3] = {0, 0, 0};
+// Token, halted-document and slice sums of documents [lo, hi).
+__device__ __forceinline__ void result_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[3],
+                                            uint64_t (*red)[kRedWaves]) {
+  for (int q = 0; q < 3; ++q) v[q] = 0;
   for (uint32_t d = lo + threadIdx.x; d < hi; d += blockDim.x) {
     v[0] += a.doc_ntok[d];
     v[1] += a.doc_halt[d] != kNone;
     v[2] += a.doc_nsl[d];
   }
   block_sum<3>(v, red);
-  if (threadIdx.x < 3) a.part[(size_t)blockIdx.x * kPartWords + 5 + threadIdx.x] = v[threadIdx.x];
 }
 
-// Results, second half: output offsets of the documents (exclusive scan), results, status;
-// the first group writes the batch's totals.
-__global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
-  __shared__ uint64_t red[6][4];
-  if (a.meta[kBad]) {  // nothing was counted: report the bad table
-    for (uint32_t d = blockIdx.x * blockDim.x + threadIdx.x; d < a.ndocs; d += gridDim.x * blockDim.x)
-      a.res[d] = DocResDev{0, 0, 0, -1, 0};
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      a.total->ntokens = 0;
-      a.total->error_offset = 0;
-      a.total->status = -1;
-      a.total->nslices = 0;
-    }
-    return;
-  }
-  uint64_t pre[3], tot[3];
-  group_prefix<3>(a.part, 5, pre, tot, red);
-  const uint64_t total = tot[0];
-  const int32_t status = total > a.cap ? -4 : 0;
-  uint64_t run = pre[0];
-  uint32_t lo, hi;
-  group_range(a.ndocs, lo, hi);
+// Output offsets of documents [lo, hi) (exclusive scan from `run`), results, status; the first
+// workgroup writes the batch's totals (tot).
+__device__ __forceinline__ void result_docs(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t run,
+                                            const uint64_t (&tot)[3], uint64_t (*red)[kRedWaves]) {
+  const int32_t status = tot[0] > a.cap ? -4 : 0;
   for (uint32_t d0 = lo; d0 < hi; d0 += blockDim.x) {  // workgroup-uniform: the scan sees every thread
     const uint32_t d = d0 + threadIdx.x;
     const bool in = d < hi;
@@ -2969,7 +2996,7 @@ __global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
       DocResDev r;
       r.tok_offset = run + v[0] - nt;
       r.ntokens = nt;
-      r.error_offset = a.docs[d].length;  // a halted document's emit replaces it
+      r.error_offset = a.doc_err[d];
       r.status = status;
       r.nslices = a.doc_nsl[d];
       a.res[d] = r;
@@ -2977,18 +3004,72 @@ __global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
     run += t[0];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.total->ntokens = total;
+    a.total->ntokens = tot[0];
     a.total->error_offset = tot[1];  // documents that did not tokenize completely
     a.total->status = status;
     a.total->nslices = (uint32_t)tot[2];
   }
 }
 
-// Emit walk of the batch: the lane emit of each lane up to its document's first halted one.
-__global__ void __launch_bounds__(256) k_bemit(BatchArgs a) {
-  if (!a.meta[kAnyLane]) return;  // every document takes the windowed emit (uniform)
-  const BatchLds l = batch_stage(a);
+// A stopped batch: nothing was counted, every record reports the bad table.
+__device__ __forceinline__ void result_bad(const BatchArgs &a) {
+  for (uint32_t d = blockIdx.x * blockDim.x + threadIdx.x; d < a.ndocs; d += gridDim.x * blockDim.x)
+    a.res[d] = DocResDev{0, 0, 0, -1, 0};
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.total->ntokens = 0;
+    a.total->error_offset = 0;
+    a.total->status = -1;
+    a.total->nslices = 0;
+  }
+}
+
+__global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
+  if (a.meta[kBad]) return;
+  const bool any = doc_pass(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+  if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;  // every writer stores the same value
+}
+
+// Results, first half: each group's sums.
+__global__ void __launch_bounds__(256) k_bscan_a(BatchArgs a) {
+  __shared__ uint64_t red[3][kRedWaves];
+  if (a.meta[kBad]) return;  // uniform: no barrier follows
+  uint32_t lo, hi;
+  group_range(a.ndocs, lo, hi);
+  uint64_t v[3];
+  result_sums(a, lo, hi, v, red);
+  if (threadIdx.x < 3) a.part[(size_t)blockIdx.x * kPartWords + 5 + threadIdx.x] = v[threadIdx.x];
+}
+
+// Results, second half.
+__global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
+  __shared__ uint64_t red[6][kRedWaves];
+  if (a.meta[kBad]) return result_bad(a);
+  uint64_t pre[3], tot[3];
+  group_prefix<3>(a.part, 5, pre, tot, red);
+  uint32_t lo, hi;
+  group_range(a.ndocs, lo, hi);
+  result_docs(a, lo, hi, pre[0], tot, red);
+}
+
+// A small batch's document pass and results in one launch of one workgroup, as k_bplan_one.
+__global__ void __launch_bounds__(1024) k_bdoc_one(BatchArgs a) {
+  __shared__ uint64_t red[3][kRedWaves];
+  if (a.meta[kBad]) return result_bad(a);
+  const bool any = doc_pass(a, threadIdx.x >> 6, blockDim.x >> 6);
+  if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;
+  __syncthreads();
+  uint64_t tot[3];
+  result_sums(a, 0, a.ndocs, tot, red);
+  result_docs(a, 0, a.ndocs, 0, tot, red);
+}
+
+// The lane emit of each lane of the documents the windowed emit does not take, up to its
+// document's first halted one, 64 lanes a wave from a queue.  The rings of the workgroup's
+// first waves fit where the windowed emit's stages go (the other waves take no part).
+__device__ __forceinline__ void batch_lane_emit(const BatchArgs &a, const BatchLds &l) {
   const uint32_t lane = threadIdx.x & 63;
+  const uint32_t waves = (blockDim.x >> 6) * kStageWords * 4 / (64 * kRingBytes);
+  if ((threadIdx.x >> 6) >= waves) return;
   const uint32_t nlanes = a.meta[kNLanes];
   const bool write = a.total->status == 0;
   for (;;) {
@@ -3006,7 +3087,7 @@ __global__ void __launch_bounds__(256) k_bemit(BatchArgs a) {
     const uint32_t off = (uint32_t)a.res[d].tok_offset + a.lane_pre[j];
     Ring r;
     r.w = reinterpret_cast<uint32_t *>(l.ring) + threadIdx.x;
-    r.stride = blockDim.x;
+    r.stride = waves * 64;
     r.kinds = a.kinds;
     r.lens = a.lens;
     r.offs = a.offs;
@@ -3018,13 +3099,8 @@ __global__ void __launch_bounds__(256) k_bemit(BatchArgs a) {
     const Tables tb{l.T, l.info, l.kind, in.sink, in.fail, in.start};
     LaneState L;
     L.cnt = 0;
-    if (in.mono) {
-      if (!r.direct && !r.offs) walk<true, true, true>(L, r, tb, src, doc.length, s, e);
-      else walk<true, true, false>(L, r, tb, src, doc.length, s, e);
-    } else {
-      if (!r.direct && !r.offs) walk<true, false, true>(L, r, tb, src, doc.length, s, e);
-      else walk<true, false, false>(L, r, tb, src, doc.length, s, e);
-    }
+    if (!r.direct && !r.offs) walk<true, false, true>(L, r, tb, src, doc.length, s, e);
+    else walk<true, false, false>(L, r, tb, src, doc.length, s, e);
     ring_flush_tail(r);
     if (j == halt) a.res[d].error_offset = L.tok;  // the halt offset, relative to the document
   }
@@ -3036,13 +3112,15 @@ __global__ void __launch_bounds__(256) k_bemit(BatchArgs a) {
 // from the count walk's checkpoint, stages the tile's tokens and writes them out coalesced,
 // exactly as the single-buffer windowed emit does with the document as its input (its
 // slices, cut at certified bytes or at the hybrid plan's serial token starts, are the
-// lanes; the document's end is the end of input).  Documents the count walk marked (a
-// halt, a fallback of a non-monotone automaton, a slice of 2^24 bytes or more) are left to
-// the lane emit.
+// lanes; the document's end is the end of input; a halted document ends with its halted
+// slice).  Documents the count walk marked (a fallback of a non-monotone automaton, a slice
+// of 2^24 bytes or more) take the lane emit, first, in the same launch.
 // A document's windowed-emit context (wave-uniform).
 struct BDoc {
   const uint8_t *src;
-  uint32_t len, mis0, nwin, lb, nl, lnom, out0, lim;
+  uint32_t len, mis0;
+  uint32_t nwin;  // windows to emit: the document's, or up to the end of its halted slice
+  uint32_t lb, nl, lnom, out0, lim;
   const uint2 *over;
   uint32_t inst;
   uint32_t sb;  // split by the hybrid plan: its first speculative lane, else kNone
@@ -3113,12 +3191,18 @@ __device__ __forceinline__ WinMeta bwin_meta(const BatchArgs &a, const BDoc &c, 
 // the following tiles' window states load while a tile walks, as in the single-buffer
 // windowed emit.
 __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
-  if (a.meta[kNoWin] || a.total->status != 0) return;  // uniform: no barrier follows
+  const bool any_lane = a.meta[kAnyLane] != 0;
+  if (!any_lane && (a.meta[kNoWin] || a.total->status != 0)) return;  // uniform: no barrier follows
   extern __shared__ __align__(16) uint8_t smem_w[];
   const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, wpb = blockDim.x >> 6;
   uint32_t *ctr = reinterpret_cast<uint32_t *>(smem_w + batch_win_lds_bytes(a.nrows, a.ninst, wpb) - 16);
   if (threadIdx.x == 0) *ctr = 0;
   const BatchLds l = batch_stage(a);  // its barrier publishes the zeroed counter
+  if (any_lane) {  // uniform
+    batch_lane_emit(a, l);
+    if (a.meta[kNoWin] || a.total->status != 0) return;
+    __syncthreads();
+  }
   uint32_t *stage = reinterpret_cast<uint32_t *>(l.ring) + wid * kStageWords;
   const uint32_t ntiles = a.meta[kNTiles];
   const uint32_t rm = refused_mask(a);
@@ -3143,15 +3227,20 @@ __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
     c.src = a.bytes + doc.offset;
     c.len = doc.length;
     c.mis0 = (uint32_t)(reinterpret_cast<uintptr_t>(c.src) & (kWin - 1));
-    c.nwin = doc_windows(reinterpret_cast<uintptr_t>(c.src), doc.length);
-    const uint32_t nt = (c.nwin + 63) / 64;
-    const uint32_t tt_lo = t - tb0, tt_hi = min(t_hi, tb0 + nt) - tb0;
+    const uint32_t nall = doc_windows(reinterpret_cast<uintptr_t>(c.src), doc.length);
+    const uint32_t nt = (nall + 63) / 64;
+    const uint32_t tt_lo = t - tb0;
+    uint32_t tt_hi = min(t_hi, tb0 + nt) - tb0;
     t = tb0 + tt_hi;  // the next segment
     if (!a.doc_win[d]) continue;
+    const uint32_t halt = a.doc_halt[d];
+    c.nwin = halt == kNone ? nall : win_from(a.ends[halt], c.mis0);
+    tt_hi = min(tt_hi, (c.nwin + 63) / 64);
+    if (tt_lo >= tt_hi) continue;
     c.lb = a.lane_base[d];
     c.nl = a.lanes_of[d];
     const bool split = spec_split(a, rm, doc);
-    c.lnom = split ? a.spec_bytes : a.lane_bytes;
+    c.lnom = split ? a.spec_bytes : a.fine_bytes;
     c.sb = split ? a.spec_base[d] : kNone;
     c.out0 = (uint32_t)a.res[d].tok_offset;
     c.lim = c.out0 + (uint32_t)a.res[d].ntokens;  // the document's outputs end here
@@ -3185,10 +3274,10 @@ __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
       const uint32_t P = __shfl(cur.tok, 0);
       const uint32_t span_end = (uint32_t)min<int64_t>((int64_t)(tt + 1) * 64 * kWin - c.mis0, c.len);
       if (in.disc)
-        win_tile<true>(tb, wa, stage, lane, cur, i, i < c.nwin, is_edge(tt), dat, wpos(tt), c.nwin, o_first, o_next,
+        win_tile<true>(tb, wa, stage, lane, cur, i, i < c.nwin, is_edge(tt), dat, wpos(tt), nall, o_first, o_next,
                        true, lane < 63 ? down : o_next, lane < 63 ? fdown : f_next, P, span_end, c.lim);
       else
-        win_tile<false>(tb, wa, stage, lane, cur, i, i < c.nwin, is_edge(tt), dat, wpos(tt), c.nwin, o_first, o_next,
+        win_tile<false>(tb, wa, stage, lane, cur, i, i < c.nwin, is_edge(tt), dat, wpos(tt), nall, o_first, o_next,
                         true, lane < 63 ? down : o_next, lane < 63 ? fdown : f_next, P, span_end, c.lim);
       cur = nxt;
       nxt = n2;
@@ -3438,18 +3527,20 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
 
 // Lanes below this walk in 64-byte stretches (walk_wave).
 constexpr uint32_t kShortLane = 512;
+// Batches: the shortest walked lane; what one workgroup plans and reports.
+constexpr uint32_t kFineLane = 128, kOneDocs = 64;
+constexpr uint64_t kOneBytes = 4u << 20;
 
 static inline void mark(hipEvent_t const *ev, int i, hipStream_t s) {
   if (ev && ev[i]) (void)hipEventRecord(ev[i], s);
 }
 
-// Workgroups of the windowed emit: 16 waves per CU in workgroups of `waves`, fewer for a
-// short input (about one tile per wave).
+// Workgroups of the windowed emit: 16 waves per CU in workgroups of `waves`, for a short input
+// one per tile (64 KiB in 17 workgroups of one busy wave each, not two of 16).
 static uint32_t win_grid(uint32_t waves, uint32_t ntiles) {
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const uint32_t want = (ntiles + waves - 1) / waves;
-  const uint32_t g = std::max<uint32_t>(1, std::min<uint32_t>(want, (uint32_t)cus * (16 / waves)));
+  const uint32_t g = std::max<uint32_t>(1, std::min<uint32_t>(ntiles, (uint32_t)cus * (16 / waves)));
   return g >= 8 ? g & ~7u : g;  // whole rounds of the 8 XCDs
 }
 
@@ -3526,9 +3617,19 @@ hipError_t run_pipeline(const DevTable &t, const CertMap &cm, const uint8_t *in,
 // only), so their length, not their number, sets the walk kernel's time.
 static uint32_t batch_spec_bytes(uint32_t) { return kSpecX; }
 
+// The lane that is walked: the plan's, over a power of two up to 64, while that gives at most
+// 64k lanes and at least kFineLane bytes.  Below about that many lanes the count pass takes as long
+// as its longest walk (73 cycles a byte), above it the lanes fill the chip and shorter ones
+// only add their unaligned ends.
+static uint32_t batch_fine_bytes(uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
+  uint32_t f = lane_bytes;
+  while (!chosen && f % 32 == 0 && f / 2 >= kFineLane && lane_bytes / f < 64 && nbytes / (f / 2) <= (64u << 10)) f /= 2;
+  return f;
+}
+
 // a document of n bytes has ceil(n / L) <= n / L + 1 lanes, L its lane length
-static uint32_t batch_max_lanes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes) {
-  const uint32_t shortest = std::min(lane_bytes, batch_spec_bytes(lane_bytes));
+static uint32_t batch_max_lanes(uint32_t ndocs, uint64_t nbytes, uint32_t fine_bytes) {
+  const uint32_t shortest = std::min(fine_bytes, batch_spec_bytes(fine_bytes));
   return (uint32_t)std::min<uint64_t>(0xFFFFFFF0ull, (uint64_t)ndocs + nbytes / shortest + 1);
 }
 
@@ -3542,15 +3643,16 @@ static uint32_t batch_max_tiles(uint32_t ndocs, uint64_t nbytes) {
   return (uint32_t)std::min<uint64_t>(0xFFFFFFF0ull, 2ull * ndocs + nbytes / (64 * kWin) + 1);
 }
 
-size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes) {
-  const uint64_t nl = batch_max_lanes(ndocs, nbytes, lane_bytes);
+size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
+  const uint32_t fine = batch_fine_bytes(nbytes, lane_bytes, chosen);
+  const uint64_t nl = batch_max_lanes(ndocs, nbytes, fine);
   const uint64_t ns = batch_max_spec(ndocs, nbytes, lane_bytes);
   const uint64_t nt = batch_max_tiles(ndocs, nbytes);
   const size_t per_doc = align256((size_t)std::max<uint32_t>(ndocs, 1) * 4);
-  return align256(kBatchMeta * 4) + align256((size_t)kDocGroups * kPartWords * 8) + 9 * per_doc + 7 * align256((size_t)nl * 4) + 3 * align256((size_t)ns * 4) +
-         align256((size_t)ns * 2 * kSpecWords * 4) + 2 * align256((size_t)ns * 16) +
-         align256((size_t)ck_slots(lane_bytes) * nl * 8) +
-         align256((size_t)nt * 64 * 8) + align256((size_t)nt * 4);
+  return align256(kBatchMeta * 4) + align256((size_t)kDocGroups * kPartWords * 8) + 10 * per_doc +
+         7 * align256((size_t)nl * 4) + 3 * align256((size_t)ns * 4) + align256((size_t)ns * 2 * kSpecWords * 4) +
+         2 * align256((size_t)ns * 16) + align256((size_t)ck_slots(fine) * nl * 8) + align256((size_t)nt * 64 * 8) +
+         align256((size_t)nt * 4);
 }
 
 size_t batch_emit_lds_bytes(int nrows, uint32_t ninst) {
@@ -3559,11 +3661,10 @@ size_t batch_emit_lds_bytes(int nrows, uint32_t ninst) {
 }
 
 hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbytes, const void *docs, uint32_t ndocs,
-                     uint32_t lane_bytes, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap, void *res,
-                     ResultDev *total, void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t const *ev) {
-  if (ws_bytes < batch_workspace_bytes(ndocs, nbytes, lane_bytes)) return hipErrorInvalidValue;
-  const size_t lds_e = batch_emit_lds_bytes(bt.nrows, bt.ninst);
-  if (!lds_e || bt.ninst == 0 || bt.ninst > (uint32_t)kMaxInst) return hipErrorInvalidValue;
+                     uint32_t lane_bytes, bool chosen, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap,
+                     void *res, ResultDev *total, void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t const *ev) {
+  if (ws_bytes < batch_workspace_bytes(ndocs, nbytes, lane_bytes, chosen)) return hipErrorInvalidValue;
+  if (!batch_emit_lds_bytes(bt.nrows, bt.ninst) || bt.ninst == 0 || bt.ninst > (uint32_t)kMaxInst) return hipErrorInvalidValue;
   BatchArgs a{};
   a.table = bt.table;
   a.rowinfo = bt.rowinfo;
@@ -3585,7 +3686,8 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   a.docs = static_cast<const DocDev *>(docs);
   a.ndocs = ndocs;
   a.lane_bytes = lane_bytes;
-  a.max_lanes = batch_max_lanes(ndocs, nbytes, lane_bytes);
+  a.fine_bytes = batch_fine_bytes(nbytes, lane_bytes, chosen);
+  a.max_lanes = batch_max_lanes(ndocs, nbytes, a.fine_bytes);
   // workspace: the per-lane arrays are sized for the most lanes the byte count allows
   uint8_t *w = static_cast<uint8_t *>(ws);
   a.meta = reinterpret_cast<uint32_t *>(w);
@@ -3598,6 +3700,7 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   a.doc_halt = reinterpret_cast<uint32_t *>(w), w += dsz;
   a.doc_ntok = reinterpret_cast<uint32_t *>(w), w += dsz;
   a.doc_nsl = reinterpret_cast<uint32_t *>(w), w += dsz;
+  a.doc_err = reinterpret_cast<uint32_t *>(w), w += dsz;
   a.spec_base = reinterpret_cast<uint32_t *>(w), w += dsz;
   a.spec_fail = reinterpret_cast<uint32_t *>(w), w += dsz;
   a.tile_base = reinterpret_cast<uint32_t *>(w), w += dsz;
@@ -3611,7 +3714,7 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   a.spec_bits = reinterpret_cast<uint32_t *>(w), w += align256((size_t)a.max_spec * 2 * kSpecWords * 4);
   a.spec_part = reinterpret_cast<uint4 *>(w), w += align256((size_t)a.max_spec * 16);
   a.spec_pre = reinterpret_cast<uint4 *>(w), w += align256((size_t)a.max_spec * 16);
-  const size_t per_lane = align256((size_t)batch_max_lanes(ndocs, nbytes, lane_bytes) * 4);
+  const size_t per_lane = align256((size_t)a.max_lanes * 4);
   a.lane_doc = reinterpret_cast<uint32_t *>(w), w += per_lane;
   a.cuts = reinterpret_cast<uint32_t *>(w), w += per_lane;
   a.ends = reinterpret_cast<uint32_t *>(w), w += per_lane;
@@ -3620,7 +3723,7 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   a.lane_pre = reinterpret_cast<uint32_t *>(w), w += per_lane;
   a.lnz = reinterpret_cast<uint32_t *>(w), w += per_lane;
   // windowed emit: checkpoints (main slots per lane, overflow per document tile), tile map
-  a.kslots = ck_slots(lane_bytes);
+  a.kslots = ck_slots(a.fine_bytes);
   a.max_tiles = batch_max_tiles(ndocs, nbytes);
   a.ck_main = reinterpret_cast<uint2 *>(w), w += align256((size_t)a.kslots * a.max_lanes * 8);
   a.ck_over = reinterpret_cast<uint2 *>(w), w += align256((size_t)a.max_tiles * 64 * 8);
@@ -3647,58 +3750,65 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, threads, lds_c) != hipSuccess || nb < 1) nb = 1;
     return (uint32_t)nb;
   };
-  const uint32_t per_cu_c = resident(reinterpret_cast<const void *>(k_bcount), 1024);
+  const bool short_lane = a.fine_bytes < kShortLane;
+  const void *count = short_lane ? reinterpret_cast<const void *>(k_bcount<64>) : reinterpret_cast<const void *>(k_bcount<128>);
+  const uint32_t per_cu_c = resident(count, 1024);
   const uint32_t per_cu_c4 = resident(reinterpret_cast<const void *>(k_bsplit), 256);
-  const uint32_t per_cu_e = (uint32_t)std::min<size_t>(8, 160 * 1024 / lds_e);
   const uint32_t gdoc = std::max<uint32_t>(1, std::min<uint32_t>(4096, (ndocs + 3) / 4));
   const uint32_t ngroups = doc_groups(ndocs);
+  // A small batch plans and reports in one workgroup each (k_bplan_one, k_bdoc_one): up to
+  // kOneDocs documents, and few enough lanes and tiles for one workgroup to number and sum.
+  const bool one = ndocs <= kOneDocs && nbytes <= kOneBytes;
+  bool refused = false;  // some instance takes the hybrid plan
+  for (uint32_t k = 0; k < bt.ninst; ++k) refused = refused || bt.inst[k].refused;
+  hipError_t e = hipSuccess;
+  auto launched = [&] { return (e = hipGetLastError()) == hipSuccess; };
   mark(ev, 0, s);
-  k_bplan_a<<<ngroups, 256, 0, s>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) {
+  if (one) {
+    k_bplan_one<<<1, 1024, 0, s>>>(a);
+    if (!launched()) return e;
+  } else {
+    k_bplan_a<<<ngroups, 256, 0, s>>>(a);
+    if (!launched()) return e;
     k_bplan_b<<<ngroups, 256, 0, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
+    if (!launched()) return e;
     k_bmap<<<gdoc, 256, 0, s>>>(a);
-    e = hipGetLastError();
+    if (!launched()) return e;
   }
   mark(ev, 1, s);
-  if (e == hipSuccess) {  // speculative walks, then the lanes of documents not split by them
-    k_bcount<<<(uint32_t)cus * per_cu_c, 1024, lds_c, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {  // the hybrid plan's cuts
-    k_bsync<<<(uint32_t)cus * 4, 256, 0, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {  // the lanes of the split documents
-    k_bsplit<<<(uint32_t)cus * per_cu_c4, 256, lds_c, s>>>(a);
-    e = hipGetLastError();
+  // speculative walks, then the lanes of documents not split by them; no more workgroups than
+  // tiles (each stages the tables)
+  const uint64_t tiles = ((uint64_t)a.max_lanes + 63) / 64 + (refused ? ((uint64_t)a.max_spec + 63) / 64 : 0);
+  const uint64_t cc = (uint64_t)cus * per_cu_c;
+  const uint32_t tc = tiles <= cc * 4 ? 256 : tiles <= cc * 8 ? 512 : 1024;
+  const uint32_t gc = (uint32_t)std::min<uint64_t>(cc, (tiles + tc / 64 - 1) / (tc / 64));
+  if (short_lane) k_bcount<64><<<gc, tc, lds_c, s>>>(a);
+  else k_bcount<128><<<gc, tc, lds_c, s>>>(a);
+  if (!launched()) return e;
+  if (refused) {
+    k_bsync<<<(uint32_t)cus * 4, 256, 0, s>>>(a);  // the hybrid plan's cuts
+    if (!launched()) return e;
+    k_bsplit<<<(uint32_t)cus * per_cu_c4, 256, lds_c, s>>>(a);  // the lanes of the split documents
+    if (!launched()) return e;
   }
   mark(ev, 2, s);
-  if (e == hipSuccess) {
+  if (one) {
+    k_bdoc_one<<<1, 1024, 0, s>>>(a);
+    if (!launched()) return e;
+  } else {
     k_bdoc<<<gdoc, 256, 0, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
+    if (!launched()) return e;
     k_bscan_a<<<ngroups, 256, 0, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
+    if (!launched()) return e;
     k_bscan_b<<<ngroups, 256, 0, s>>>(a);
-    e = hipGetLastError();
+    if (!launched()) return e;
   }
   mark(ev, 3, s);
-  if (e == hipSuccess) {  // the lane emit: documents the windowed emit does not take
-    k_bemit<<<(uint32_t)cus * per_cu_e, 256, lds_e, s>>>(a);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess && win_waves) {  // the windowed emit: 16 waves per CU as LDS allows
-    k_bemit_win<<<(uint32_t)cus * (16 / win_waves), win_waves * 64, batch_win_lds_bytes(bt.nrows, bt.ninst, win_waves),
-                  s>>>(a);
-    e = hipGetLastError();
-  }
+  // the windowed emit, and the lane emit of what it leaves: 16 waves per CU as LDS allows
+  // (win_waves is at least 4 where the lane emit's rings fit, which lex_batch_create requires)
+  const uint32_t ge = (uint32_t)std::min<uint64_t>((uint64_t)cus * (16 / win_waves), (uint64_t)a.max_tiles);
+  k_bemit_win<<<ge, win_waves * 64, batch_win_lds_bytes(bt.nrows, bt.ninst, win_waves), s>>>(a);
+  (void)launched();
   mark(ev, 4, s);
   return e;
 }

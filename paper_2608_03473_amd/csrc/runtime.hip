@@ -587,7 +587,7 @@ static int batch_lane_bytes(const lex_run_opts *o, uint64_t nbytes, uint32_t &lb
 size_t lex_batch_workspace_size(const lex_batch *b, uint32_t ndocs, uint64_t nbytes, const lex_run_opts *opts) {
   uint32_t lb = 0;
   if (!b || nbytes > 0xFFFFFFF0ull || batch_lane_bytes(opts, nbytes, lb) != LEX_OK) return 0;
-  return lexk::batch_workspace_bytes(ndocs, nbytes, lb);
+  return lexk::batch_workspace_bytes(ndocs, nbytes, lb, opts && opts->lane_bytes);
 }
 
 int lex_run_batch(const lex_batch *b, const uint8_t *d_bytes, uint64_t nbytes, const lex_doc *d_docs, uint32_t ndocs,
@@ -600,12 +600,13 @@ int lex_run_batch(const lex_batch *b, const uint8_t *d_bytes, uint64_t nbytes, c
   uint32_t lb = 0;
   int rc = batch_lane_bytes(opts, nbytes, lb);
   if (rc != LEX_OK) return rc;
-  if (ws_bytes < lexk::batch_workspace_bytes(ndocs, nbytes, lb)) return LEX_ELIMIT;
+  const bool chosen = opts && opts->lane_bytes;
+  if (ws_bytes < lexk::batch_workspace_bytes(ndocs, nbytes, lb, chosen)) return LEX_ELIMIT;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != b->device) return LEX_EDEVICE;
   hipEvent_t const *ev = opts && opts->events ? reinterpret_cast<hipEvent_t const *>(opts->events) : nullptr;
-  hipError_t e = lexk::run_batch(b->bt, d_bytes, nbytes, d_docs, ndocs, lb, d_kinds, d_lens, d_offsets, cap, d_res,
-                                 reinterpret_cast<lexk::ResultDev *>(d_total), d_ws, ws_bytes,
+  hipError_t e = lexk::run_batch(b->bt, d_bytes, nbytes, d_docs, ndocs, lb, chosen, d_kinds, d_lens, d_offsets, cap,
+                                 d_res, reinterpret_cast<lexk::ResultDev *>(d_total), d_ws, ws_bytes,
                                  static_cast<hipStream_t>(stream), ev);
   return e == hipSuccess ? LEX_OK : LEX_EDEVICE;
 }
