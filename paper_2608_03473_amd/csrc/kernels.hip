@@ -933,6 +933,23 @@ __device__ __forceinline__ bool walk_wave(LaneState &L, const Tables &tb, const 
   return halted;
 }
 
+constexpr uint32_t kSpecX = 2048;  // the sync window; at most the speculative lane
+
+// The hybrid plan's state cuts (see k_hstate): lanes of wpl windows, state blocks of them.
+constexpr uint32_t kStWarm = 16, kStLanes = 256 - kStWarm;  // warm-up and own lanes of a workgroup
+struct StateArgs {
+  uint32_t wpl, nlanes, nblocks;  // windows per lane (a power of two, at least 4)
+  uint32_t S, ncoarse;            // the plan's speculative lane and their number
+  uint32_t checks;                // workgroups of the windowed emit that check the plan's cuts
+  uint2 *ck;                      // per window: row, count since the lane's start, token start
+  uint32_t *lane_pre;             // nlanes: exclusive prefix of counts in the block
+  uint64_t *blk_sum;              // nblocks: counts (k_hstate), their exclusive prefix (k_hscan)
+  uint32_t *blk_fail;             // first halted lane or ~0u
+  uint2 *blk_halt;                // its failed token's start, its block's tokens up to the halt
+  uint32_t *blk_fb;               // some lane fell back
+  uint2 *blk_a, *blk_z;           // row and token start at the first own lane's start, the last's end
+};
+
 struct WalkArgs {
   const uint32_t *table;  // global copies, staged into LDS
   const uint8_t *rowinfo;
@@ -965,6 +982,9 @@ struct WalkArgs {
   FastDiv lane_div;       // division by lane_bytes
   uint64_t *chunk_st;     // one pass: look-back status per workgroup of lanes
   uint32_t *chunk_ctr;    // one pass: next workgroup of lanes to take
+  StateArgs hs;           // hybrid plan
+  const uint32_t *cond;   // hybrid plan's second route: run only if *cond (null: always)
+  const uint32_t *spec_cut, *spec_fail;  // and its cuts, or one slice (null: planned cuts)
   // emit
   const uint32_t *meta;
   ResultDev *res;
@@ -1100,8 +1120,14 @@ __device__ __forceinline__ uint32_t plan_lanes(const WalkArgs &a, uint32_t c0, c
   s = e = (uint32_t)min<uint64_t>(x, a.n);
   if (j < a.nlanes) {
     if (!FUSED) {
-      s = a.cuts[j];
-      e = a.cuts[j + 1];
+      if (a.spec_cut) {  // the hybrid plan's second route
+        const bool one = *a.spec_fail != 0;
+        s = one ? (j ? a.n : 0) : a.spec_cut[j];
+        e = one || j + 1 == a.nlanes ? a.n : a.spec_cut[j + 1];
+      } else {
+        s = a.cuts[j];
+        e = a.cuts[j + 1];
+      }
       if (s < e) start = s;
     } else if (j == 0) {
       start = a.n ? 0 : kNone;
@@ -1191,6 +1217,7 @@ __device__ __forceinline__ void count_lanes(const WalkArgs &a, const Tables &tb,
 // CK: record checkpoints for the windowed emit.
 template <int LINE, bool FUSED, bool CK>
 __global__ void __launch_bounds__(1024) k_count(WalkArgs a) {
+  if (!FUSED && a.cond && !*a.cond) return;  // uniform
   const Lds l = carve_lds(a.nrows);
   stage_tables(a, l, FUSED);
   const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
@@ -1198,7 +1225,7 @@ __global__ void __launch_bounds__(1024) k_count(WalkArgs a) {
   const uint32_t c0 = blockIdx.x * blockDim.x, j = c0 + threadIdx.x;
   uint32_t s, e, rank;
   const uint32_t total = plan_lanes<FUSED>(a, c0, l.lut, q, s, e, rank);
-  if (FUSED && j < a.nlanes) {
+  if ((FUSED || a.spec_cut) && j < a.nlanes) {
     a.cuts[j] = s;
     a.ends[j] = e;
   }
@@ -1233,15 +1260,15 @@ __global__ void __launch_bounds__(1024) k_count(WalkArgs a) {
   }
 }
 
-// (d) One workgroup: exclusive scan of block sums (in place), first halted lane,
+// (d) One workgroup of 1024 threads: exclusive scan of block sums (in place), first halted lane,
 // output length, status.
-__global__ void __launch_bounds__(1024) k_scan(uint64_t *__restrict__ blk_sum, const uint32_t *__restrict__ blk_fail,
-                                               const uint32_t *__restrict__ blk_nonempty,
-                                               const uint32_t *__restrict__ blk_big,
-                                               int32_t *__restrict__ blk_lnz, uint32_t nblocks,
-                                               uint32_t block, const uint32_t *__restrict__ counts,
-                                               const uint32_t *__restrict__ blk_tok, uint32_t *__restrict__ meta,
-                                               ResultDev *__restrict__ res, uint64_t cap, uint32_t n) {
+__device__ __forceinline__ void scan_blocks(uint64_t *__restrict__ blk_sum, const uint32_t *__restrict__ blk_fail,
+                                            const uint32_t *__restrict__ blk_nonempty,
+                                            const uint32_t *__restrict__ blk_big,
+                                            int32_t *__restrict__ blk_lnz, uint32_t nblocks,
+                                            uint32_t block, const uint32_t *__restrict__ counts,
+                                            const uint32_t *__restrict__ blk_tok, uint32_t *__restrict__ meta,
+                                            ResultDev *__restrict__ res, uint64_t cap, uint32_t n) {
   // each thread folds a contiguous range of workgroups; the ranges' sums, minima and maxima
   // are scanned inclusively within each wave by shuffles, across the waves through LDS
   __shared__ uint64_t wsum[16];
@@ -1327,6 +1354,15 @@ __global__ void __launch_bounds__(1024) k_scan(uint64_t *__restrict__ blk_sum, c
     res->status = ntok > cap ? -4 : 0;
     res->nslices = pn + in;
   }
+}
+
+__global__ void __launch_bounds__(1024) k_scan(uint64_t *__restrict__ blk_sum, const uint32_t *__restrict__ blk_fail,
+                                               const uint32_t *__restrict__ blk_nonempty,
+                                               const uint32_t *__restrict__ blk_big, int32_t *__restrict__ blk_lnz,
+                                               uint32_t nblocks, uint32_t block, const uint32_t *__restrict__ counts,
+                                               const uint32_t *__restrict__ blk_tok, uint32_t *__restrict__ meta,
+                                               ResultDev *__restrict__ res, uint64_t cap, uint32_t n) {
+  scan_blocks(blk_sum, blk_fail, blk_nonempty, blk_big, blk_lnz, nblocks, block, counts, blk_tok, meta, res, cap, n);
 }
 
 // The lane emit of lane j: its slice walked again from its certified start, its tokens
@@ -1465,6 +1501,81 @@ __device__ __forceinline__ WinMeta win_meta(const WalkArgs &a, const WinR1 &r, u
   m.tok = c.y;
   m.out = base + (c.x & 0xFFFFFFu);
   return m;
+}
+
+// The same from the hybrid plan's state cuts: every window has its own checkpoint.
+__device__ __forceinline__ WinMeta state_meta(const WalkArgs &a, uint32_t i, uint32_t nwin, uint32_t ntok) {
+  WinMeta m{0, 0, ntok, 0};
+  if (i >= nwin) return m;
+  const uint32_t k = i / a.hs.wpl;
+  const uint2 c = a.hs.ck[i];
+  m.st = row_state(c.x >> 24);
+  m.tok = c.y;
+  m.out = (uint32_t)a.hs.blk_sum[k / kStLanes] + a.hs.lane_pre[k] + (c.x & 0xFFFFFFu);
+  return m;
+}
+
+// The hybrid plan's cuts, a thread per speculative lane k > 0 of S bytes: the plan cuts there at
+// the first position in [k S, k S + kSpecX) that starts a token both of the serial scan (known
+// here from the state cuts) and of a walk begun at k S, as walk_spec runs it; without one it
+// takes the text as one slice, or, at the last lane, one slice less.  Only the reported number of
+// slices depends on it.  Both scans are the same from such a position on, so they have one
+// before a window's start (or the text's end) exactly when they are there in the same row and
+// token: only the second walk is run, against the windows' checkpoints, in 16-byte blocks (most
+// boundaries agree at the first or second window; comparing the two token by token took 490 us
+// for 32 MiB, several times the emit beside it).
+__device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) {
+  if (threadIdx.x >= 256) return;  // one wave per SIMD: a chain of dependent steps
+  const uintptr_t base = reinterpret_cast<uintptr_t>(a.in);
+  const uint32_t mis0 = (uint32_t)(base & (kWin - 1));
+  const uint2 z = a.hs.blk_z[a.hs.nblocks - 1];  // the serial scan at the text's end
+  for (uint32_t k = 1 + blockIdx.x * 256 + threadIdx.x; k < a.hs.ncoarse; k += a.hs.checks * 256) {
+    const uint32_t c = k * a.hs.S, end = (uint32_t)min<uint64_t>((uint64_t)c + kSpecX, a.n);
+    const uint32_t bend = (uint32_t)min<uint64_t>((uint64_t)c + a.hs.S + kSpecX, a.n);  // the walk's end
+    uint32_t st = tb.start, p = c, tok = c, lacc = c;
+    bool same = false;
+    int64_t nb = INT64_MIN;  // position of the block loaded ahead
+    uint4 nv = make_uint4(0, 0, 0, 0);
+    while (tok < end) {
+      if (p >= bend) {
+        same = bend == a.n && st == z.x && tok == z.y;
+        break;
+      }
+      const uint32_t lo = (uint32_t)((base + p) & 15);
+      const int64_t blk = (int64_t)p - lo;
+      const uint32_t hi = (uint32_t)min<int64_t>(16, (int64_t)bend - blk);
+      const uint4 v = blk == nb ? nv : load_block(a.in, blk, a.n);
+      nb = blk + 16;
+      nv = load_block(a.in, nb, a.n);
+      uint32_t m = 0, ac = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < 16; ++q) {
+        const uint32_t y = entry_from(tb, st, byte_of(v, q));
+        const bool in = q >= lo && q < hi;
+        const uint32_t e = in ? y : 0;
+        st = in ? y : st;
+        m = __builtin_amdgcn_alignbit(e, m, 2);
+        ac = __builtin_amdgcn_alignbit(e >> 7, ac, 1);
+      }
+      st &= kRowMask;
+      const uint32_t me = m & 0xAAAAAAAAu;
+      tok = me ? (uint32_t)blk + ((31 - __clz(me)) >> 1) : tok;
+      lacc = ac ? (uint32_t)blk + (31 - __clz(ac)) - 15 : lacc;
+      p = (uint32_t)(blk + hi);
+      if (st == tb.sink || st == tb.fail) {  // restart, as walk_spec does
+        p = tok = st == tb.fail && tb.fail != tb.sink && lacc > tok ? lacc : tok + 1;
+        lacc = p;
+        st = tb.start;
+      } else if (p < a.n && ((base + p) & (kWin - 1)) == 0) {
+        const uint2 w = a.hs.ck[(p + (uint64_t)mis0) / kWin];
+        if (row_state(w.x >> 24) == st && w.y == tok && tok < end) {
+          same = true;
+          break;
+        }
+      }
+    }
+    if (!same) atomicMin(&a.res->nslices, k + 1 == a.hs.ncoarse ? a.hs.ncoarse - 1 : 1u);
+  }
 }
 
 // Output of the staged and the direct walk.
@@ -1658,14 +1769,26 @@ __device__ __forceinline__ void win_tile(const Tables &tb, const WalkArgs &a, ui
 // write nothing).  A slice too long for the checkpoints, or one that fell back, takes the lane
 // emit instead, in the same launch: each thread emits lanes j, j + the grid's threads, ... up
 // to the first halted lane.
-template <bool DISC, bool MONO>
+//
+// HYB: the scan of a refused set.  Its windows come from the state cuts where they stand, and
+// the launch's first workgroups check the plan's own cuts meanwhile (check_cuts).
+template <bool DISC, bool MONO, bool HYB>
 __global__ void __launch_bounds__(1024) k_emit_win(WalkArgs a) {
   const uint32_t first = a.meta[0];
+  const bool state = HYB && a.meta[2] == 0;
+  const uint32_t bid = HYB ? blockIdx.x - a.hs.checks : blockIdx.x, nb = HYB ? gridDim.x - a.hs.checks : gridDim.x;
   const Lds l = carve_lds(a.nrows);
+  if (HYB && blockIdx.x < a.hs.checks) {  // uniform
+    if (!state || first != kNone || a.n == 0) return;
+    stage_tables(a, l, false);
+    const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
+    check_cuts(a, tb);
+    return;
+  }
   if (a.meta[1] != 0) {  // uniform
     stage_tables(a, l, false);
     const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
-    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < a.nlanes && j <= first; j += gridDim.x * blockDim.x)
+    for (uint32_t j = bid * blockDim.x + threadIdx.x; j < a.nlanes && j <= first; j += nb * blockDim.x)
       emit_lane<MONO>(a, tb, l.ring, j, first);
     return;
   }
@@ -1679,11 +1802,11 @@ __global__ void __launch_bounds__(1024) k_emit_win(WalkArgs a) {
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.in);
   const uint32_t mis0 = (uint32_t)(base & (kWin - 1));
   const uint32_t nall = (uint32_t)(((uint64_t)a.n + mis0 + kWin - 1) / kWin);
-  const uint32_t nwin = first == kNone ? nall : win_from(a.ends[first], mis0);
+  const uint32_t nwin = first == kNone ? nall : state ? min(nall, (first + 1) * a.hs.wpl) : win_from(a.ends[first], mis0);
   const uint32_t ntiles = (nwin + 63) / 64;
   const uint32_t ntok = (uint32_t)a.res->ntokens;  // every store below stays under it
-  const uint32_t per = (ntiles + gridDim.x - 1) / gridDim.x;
-  const uint32_t g_lo = min(ntiles, blockIdx.x * per), g_hi = min(ntiles, g_lo + per);
+  const uint32_t per = (ntiles + nb - 1) / nb;
+  const uint32_t g_lo = min(ntiles, bid * per), g_hi = min(ntiles, g_lo + per);
   bool more = true;
   auto take = [&]() -> uint32_t {  // the wave's next tile (wave-uniform), kNone at the end
     if (!more) return kNone;
@@ -1700,10 +1823,15 @@ __global__ void __launch_bounds__(1024) k_emit_win(WalkArgs a) {
   if (id0 == kNone) return;  // wave-uniform, and no workgroup barrier follows
   auto win_of = [&](uint32_t t) { return t == kNone ? nwin : t * 64 + lane; };
   auto after = [&](uint32_t t) { return t == kNone ? nwin : min(nwin, (t + 1) * 64); };  // uniform
-  auto meta_of = [&](uint32_t i) { return win_meta(a, win_r1(a, i, mis0, nwin), i, nwin, ntok); };
+  // first and second rounds; a state cut's window needs one round (its own checkpoint)
+  auto round1 = [&](uint32_t i) { return HYB && state ? WinR1{} : win_r1(a, i, mis0, nwin); };
+  auto round2 = [&](const WinR1 &r, uint32_t i) {
+    return HYB && state ? state_meta(a, i, nwin, ntok) : win_meta(a, r, i, nwin, ntok);
+  };
+  auto meta_of = [&](uint32_t i) { return round2(round1(i), i); };
   WinMeta cur = meta_of(win_of(id0)), cx = meta_of(after(id0));
   WinMeta nxt = meta_of(win_of(id1)), nx = meta_of(after(id1));
-  WinR1 r1 = win_r1(a, win_of(id2), mis0, nwin), r1x = win_r1(a, after(id2), mis0, nwin);
+  WinR1 r1 = round1(win_of(id2)), r1x = round1(after(id2));
   auto wpos = [&](uint32_t t) { return (int64_t)t * 64 * kWin + (int64_t)lane * kWin - mis0; };
   auto is_edge = [&](uint32_t t) { return t == 0 || t + 1 == ntiles; };  // (also when nwin < nall)
   Win64 dat = is_edge(id0) ? win_load<true>(a.in, wpos(id0), a.n) : win_load<false>(a.in, wpos(id0), a.n);
@@ -1714,10 +1842,10 @@ __global__ void __launch_bounds__(1024) k_emit_win(WalkArgs a) {
       ndat = is_edge(id1) ? win_load<true>(a.in, wpos(id1), a.n) : win_load<false>(a.in, wpos(id1), a.n);
     // the state of the tile after next, and the first-round loads of the one after that:
     // issued here, they complete while this tile walks
-    const WinMeta n2 = win_meta(a, r1, win_of(id2), nwin, ntok), n2x = win_meta(a, r1x, after(id2), nwin, ntok);
+    const WinMeta n2 = round2(r1, win_of(id2)), n2x = round2(r1x, after(id2));
     const uint32_t id3 = take();
-    r1 = win_r1(a, win_of(id3), mis0, nwin);
-    r1x = win_r1(a, after(id3), mis0, nwin);
+    r1 = round1(win_of(id3));
+    r1x = round1(after(id3));
     // this window's range of output slots ends where the next window's begins
     // (every shuffle runs with the whole wave active: a lane reading from an inactive
     // lane gets no defined value)
@@ -2052,7 +2180,6 @@ __global__ void k_onepass_reset(uint64_t *st, uint32_t n, uint32_t *ctr) {
 // its own cut (the serial scan halts there: the one-lane scan then reports the error as
 // usual).
 constexpr int kMaxInst = 8;
-constexpr uint32_t kSpecX = 2048;  // the sync window; at most the speculative lane
 constexpr uint32_t kSpecWords = kSpecX / 32;
 
 struct BatchInst {
@@ -3288,24 +3415,255 @@ __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
 }
 
 // ------------------------------------------------- hybrid plan for a single buffer
-// The hybrid plan (see the batch notes above) for one buffer of a refused set: lane k walks
-// [k S, (k+1) S + kSpecX) speculatively (k_hspec), k_hsync finds the cuts, and k_hcuts
-// writes them as the planned lane boundaries, or {0, n, ..., n} (one slice) when the plan
-// falls back.  The count walk, scan and emit of the pipeline path then run unchanged.
+// A refused set has no certified byte to cut at.  Its scan is cut by state instead (k_hstate):
+// a lane is a fixed run of windows, walked from the row and token start that the lane before it
+// ends in.  That state is first guessed, by a walk over the kStWarm windows before the lane from
+// the start row (text like this falls into step with its serial scan within a few tokens), then
+// compared with the end of the lane before, and a lane that guessed wrong is walked again from
+// the right one until all of a workgroup's lanes agree.  A workgroup guesses its first lane
+// from 16 warm-up lanes before it, which it walks and compares the same way, and k_hscan
+// compares the workgroups' ends.  The lanes' counts and checkpoints are then the serial scan's,
+// and the windowed emit runs from them: the text is walked 1.25 to 2 times instead of 2.5, in
+// chains of 512 to 1280 steps instead of 6144 plus 4096.
+//
+// The second route is the plan by speculative lanes and token cuts (see the batch notes above):
+// lane k walks [k S, (k+1) S + kSpecX) speculatively (k_hspec), k_hsync finds the cuts, and the
+// count walk takes them as its lanes' boundaries, or {0, n, ..., n} (one slice) when the plan
+// falls back; scan and emit of the pipeline path follow.  It is taken when a lane met FAIL (longest
+// match falls back across lanes), when the workgroups do not agree, and by scans without the
+// windowed emit.
 struct HybridArgs {
   const uint8_t *in;
   uint32_t n, nlanes, S;
   uint32_t *cut, *rst, *bits, *fail;  // per lane: cut, last restart, head then tail; one flag
-  uint32_t *cuts;                     // nlanes + 1 lane boundaries
+  uint32_t *meta;
 };
 
-__global__ void __launch_bounds__(256) k_hspec(WalkArgs a, HybridArgs h) {
+// One window's 64 bytes walked from (st, tok), counting into cnt; positions outside [0, n) are
+// held when EDGE.  RESET: a dead end restarts at the next 16-byte block (a guess, not a scan).
+template <bool EDGE, bool RESET>
+__device__ __forceinline__ void state_window(const Tables &tb, const Win64 &d, int64_t wp, uint32_t n, uint32_t &st,
+                                             uint32_t &tok, uint32_t &cnt) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t m = 0;
+    const int64_t P = wp + 16 * i;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const uint32_t y = entry_from(tb, st, byte_of(d.v[i], k));
+      const bool in = !EDGE || (P + k >= 0 && P + k < (int64_t)n);
+      st = in ? y : st;
+      m = __builtin_amdgcn_alignbit(in ? y : 0u, m, 2);
+    }
+    st &= kRowMask;
+    cnt += __builtin_popcount(m & 0x55555555u);
+    const uint32_t me = m & 0xAAAAAAAAu;
+    tok = me ? (uint32_t)P + ((31 - __clz(me)) >> 1) : tok;
+    if (RESET && (st == tb.sink || st == tb.fail)) {
+      st = tb.start;
+      tok = (uint32_t)max<int64_t>(0, P + 16);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_hstate(WalkArgs a) {
   const Lds l = carve_lds(a.nrows);
   stage_tables(a, l, false);
   const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
-  const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid == 0) *h.fail = 0;
-  for (uint32_t k = gid; k < h.nlanes; k += gridDim.x * blockDim.x) {
+  uint32_t *zst = reinterpret_cast<uint32_t *>(l.ring), *ztok = zst + 256;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t mis0 = (uint32_t)(reinterpret_cast<uintptr_t>(a.in) & (kWin - 1));
+  const uint32_t nall = (uint32_t)(((uint64_t)a.n + mis0 + kWin - 1) / kWin), wpl = a.hs.wpl;
+  const int64_t kk = (int64_t)blockIdx.x * kStLanes + tid - kStWarm;  // this thread's lane
+  const bool in = kk >= 0 && kk < (int64_t)a.hs.nlanes, own = in && tid >= kStWarm;
+  const uint32_t k = in ? (uint32_t)kk : 0, i0 = k * wpl, i1 = in ? min(nall, i0 + wpl) : 0;
+  auto wpos = [&](uint32_t i) { return (int64_t)i * kWin - mis0; };
+  auto inside = [&](uint32_t i) { return wpos(i) >= 0 && wpos(i) + kWin <= (int64_t)a.n; };
+  auto load = [&](uint32_t i) { return inside(i) ? win_load<false>(a.in, wpos(i), a.n) : win_load<true>(a.in, wpos(i), a.n); };
+  auto dead = [&](uint32_t st) { return st == tb.sink || st == tb.fail; };
+  Win64 dat{};
+  // the guess: lane 0 starts at the start row, others walk the four windows before
+  uint32_t st = tb.start, tok = 0, cnt = 0;
+  if (k) dat = load(i0 - 4);
+  for (uint32_t w = 0; w < 4; ++w) {
+    const Win64 cur = dat;
+    if (in) dat = load(k ? i0 - 3 + w : 0);  // (the last round loads the lane's own first window)
+    uint32_t s2 = st, t2 = tok, c2 = 0;
+    if (k && w == 0) t2 = (uint32_t)max<int64_t>(0, wpos(i0 - 4));
+    state_window<false, true>(tb, cur, k ? wpos(i0 - 4 + w) : 0, a.n, s2, t2, c2);
+    st = k ? s2 : st;
+    tok = k ? t2 : tok;
+  }
+  // walks the lane from (st, tok), recording every window's checkpoint
+  auto run = [&](bool act) {
+    cnt = act ? 0 : cnt;
+    for (uint32_t w = 0; w < wpl; ++w) {
+      const uint32_t i = i0 + w;
+      const bool mine = act && i < i1;
+      const Win64 cur = dat;
+      if (act && i + 1 < i1) dat = load(i + 1);
+      if (mine) a.hs.ck[i] = make_uint2(((st >> kRowShift) << 24) | cnt, tok);
+      uint32_t s2 = st, t2 = tok, c2 = cnt;
+      if (__all(!mine || inside(i))) state_window<false, false>(tb, cur, wpos(i), a.n, s2, t2, c2);
+      else state_window<true, false>(tb, cur, wpos(i), a.n, s2, t2, c2);
+      st = mine ? s2 : st;
+      tok = mine ? t2 : tok;
+      cnt = mine ? c2 : cnt;
+    }
+  };
+  uint32_t as = st, at = tok;  // the state the lane was walked from
+  run(in);
+  for (;;) {  // each round settles at least the first lane that disagrees: at most 256
+    zst[tid] = st;
+    ztok[tid] = tok;
+    __syncthreads();
+    bool again = false;
+    if (in && tid && k) {
+      const uint32_t ps = zst[tid - 1], pt = ztok[tid - 1];
+      // (past a halt, and past a warm-up lane that guessed its way into a dead end, nothing is known)
+      again = !dead(ps) && (ps != as || pt != at);
+      if (again) as = ps, at = pt;
+    }
+    const bool wave = __any(again);
+    if (lane == 0) l.red32[wid] = wave;
+    __syncthreads();
+    if (!(l.red32[0] | l.red32[1] | l.red32[2] | l.red32[3])) break;
+    if (wave) {
+      if (again) {
+        st = as;
+        tok = at;
+        dat = load(i0);
+      }
+      run(again);
+    }
+  }
+  // the text's end, halts and fallbacks of own lanes (those past the first halt do not count)
+  bool halted = own && st == tb.sink, fell = own && st == tb.fail && tb.fail != tb.sink;
+  if (own && i0 < nall && i1 == nall && !dead(st) && st != tb.start) {
+    const uint32_t row = st >> kRowShift;
+    if (tb.info[row] & kInfoAcc) cnt += tb.info[row] & kInfoCount ? 1 : 0;
+    else if (tb.fail == tb.sink) halted = true;
+    else fell = true;
+  }
+  const uint32_t mine = own ? cnt : 0;
+  uint32_t incl = mine, F = halted ? k : kNone;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t v = __shfl_up(incl, d);
+    if (lane >= d) incl += v;
+  }
+  for (int d = 32; d; d >>= 1) F = min(F, (uint32_t)__shfl_xor((int)F, d));
+  if (lane == 63) l.red64[wid] = incl;
+  if (lane == 0) l.red32[4 + wid] = F;
+  __syncthreads();
+  uint32_t pre = 0;
+  uint64_t sum = 0;
+  F = kNone;
+  for (uint32_t w = 0; w < 4; ++w) {
+    pre += w < wid ? (uint32_t)l.red64[w] : 0;
+    sum += l.red64[w];
+    F = min(F, l.red32[4 + w]);
+  }
+  if (own) a.hs.lane_pre[k] = pre + incl - mine;
+  const bool fb = __any(fell && k < F);
+  if (lane == 0) l.red32[8 + wid] = fb;
+  if (own && k == F) a.hs.blk_halt[blockIdx.x] = make_uint2(tok, pre + incl);
+  if (tid == kStWarm) a.hs.blk_a[blockIdx.x] = make_uint2(as, at);
+  if (own && (tid == 255 || k + 1 == a.hs.nlanes)) a.hs.blk_z[blockIdx.x] = make_uint2(st, tok);
+  __syncthreads();
+  if (tid == 0) {
+    a.hs.blk_sum[blockIdx.x] = sum;
+    a.hs.blk_fail[blockIdx.x] = F;
+    a.hs.blk_fb[blockIdx.x] = l.red32[8] | l.red32[9] | l.red32[10] | l.red32[11];
+  }
+}
+
+// Whether the state cuts stand: up to the first halt no block fell back, and each starts in the
+// state the one before ends in.  f: the first halted lane.  Every thread of the workgroup calls
+// this; red: 32 words of LDS.
+__device__ __forceinline__ bool state_stands(const StateArgs &h, uint32_t *red, uint32_t &f) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  uint32_t bad = kNone;
+  f = kNone;
+  for (uint32_t i = threadIdx.x; i < h.nblocks; i += blockDim.x) {
+    f = min(f, h.blk_fail[i]);
+    const uint2 x = h.blk_a[i], y = i ? h.blk_z[i - 1] : x;
+    if (h.blk_fb[i] || x.x != y.x || x.y != y.y) bad = min(bad, i);
+  }
+  for (int d = 32; d; d >>= 1) {
+    f = min(f, (uint32_t)__shfl_xor((int)f, d));
+    bad = min(bad, (uint32_t)__shfl_xor((int)bad, d));
+  }
+  if (lane == 0) red[wid] = f, red[16 + wid] = bad;
+  __syncthreads();
+  for (uint32_t w = 0; w < nw; ++w) {
+    f = min(f, red[w]);
+    bad = min(bad, red[16 + w]);
+  }
+  __syncthreads();
+  return bad == kNone || (f != kNone && bad > f / kStLanes);
+}
+
+// One workgroup: the scan of whichever route was taken.  State cuts: the blocks' exclusive
+// prefixes and the result, with the plan's number of slices before check_cuts.
+__global__ void __launch_bounds__(1024) k_hscan(WalkArgs a, uint32_t *__restrict__ meta) {
+  __shared__ uint64_t wsum[16];
+  __shared__ uint32_t red[32];
+  if (meta[2]) {  // uniform
+    scan_blocks(a.blk_sum, a.blk_fail, a.blk_nonempty, a.blk_big, a.blk_lnz, (a.nlanes + a.block - 1) / a.block, a.block,
+                a.counts, a.blk_tok, meta, a.res, a.cap, a.n);
+    return;
+  }
+  const StateArgs &h = a.hs;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  uint32_t f;
+  (void)state_stands(h, red, f);
+  const uint32_t per = (h.nblocks + 1023) / 1024;
+  const uint32_t lo = min(h.nblocks, tid * per), hi = min(h.nblocks, lo + per);
+  uint64_t s = 0;
+  for (uint32_t i = lo; i < hi; ++i) s += h.blk_sum[i];
+  uint64_t is = s;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t v = __shfl_up(is, d);
+    if (lane >= (uint32_t)d) is += v;
+  }
+  if (lane == 63) wsum[wid] = is;
+  __syncthreads();
+  uint64_t run = is - s, total = 0;
+  for (uint32_t w = 0; w < 16; ++w) {
+    run += w < wid ? wsum[w] : 0;
+    total += wsum[w];
+  }
+  for (uint32_t i = lo; i < hi; ++i) {
+    const uint64_t x = h.blk_sum[i];
+    h.blk_sum[i] = run;
+    run += x;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t b = f / kStLanes;
+    const uint2 halt = f == kNone ? make_uint2(a.n, 0) : h.blk_halt[b];
+    const uint64_t ntok = f == kNone ? total : h.blk_sum[b] + halt.y;
+    meta[0] = f;
+    meta[1] = 0;
+    a.res->ntokens = ntok;
+    a.res->error_offset = halt.x;
+    a.res->status = ntok > a.cap ? -4 : 0;
+    a.res->nslices = f == kNone ? h.ncoarse : 1;  // a halt makes the plan fall back
+  }
+}
+
+__global__ void __launch_bounds__(256) k_hspec(WalkArgs a, HybridArgs h) {
+  const Lds l = carve_lds(a.nrows);
+  if (a.hs.nblocks) {
+    uint32_t f;
+    const bool stands = state_stands(a.hs, l.red32, f);
+    if (blockIdx.x == 0 && threadIdx.x == 0) h.meta[2] = !stands;
+    if (stands) return;  // uniform
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *h.fail = 0;
+  stage_tables(a, l, false);
+  const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
+  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < h.nlanes; k += gridDim.x * blockDim.x) {
     const uint32_t b = k * h.S;
     const uint32_t b2 = (uint32_t)min<uint64_t>((uint64_t)(k + 1) * h.S, h.n);
     const uint32_t end = (uint32_t)min<uint64_t>((uint64_t)b2 + kSpecX, h.n);
@@ -3317,7 +3675,8 @@ __global__ void __launch_bounds__(256) k_hspec(WalkArgs a, HybridArgs h) {
   }
 }
 
-__global__ void __launch_bounds__(256) k_hsync(HybridArgs h) {
+__global__ void __launch_bounds__(256) k_hsync(HybridArgs h, const uint32_t *cond) {
+  if (cond && !*cond) return;
   for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < h.nlanes; k += gridDim.x * blockDim.x) {
     uint32_t cut = 0;
     bool ok = true;
@@ -3336,12 +3695,6 @@ __global__ void __launch_bounds__(256) k_hsync(HybridArgs h) {
     h.cut[k] = cut;
     if (!ok) *h.fail = 1;
   }
-}
-
-__global__ void __launch_bounds__(256) k_hcuts(HybridArgs h) {
-  const bool fail = *h.fail != 0;
-  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k <= h.nlanes; k += gridDim.x * blockDim.x)
-    h.cuts[k] = k == h.nlanes ? h.n : fail ? (k ? h.n : 0) : h.cut[k];
 }
 
 }  // namespace
@@ -3436,7 +3789,7 @@ bool carve(void *ws, size_t ws_bytes, uint32_t n, uint32_t lane_bytes, uint32_t 
   p.blk_lnz = reinterpret_cast<int32_t *>(b + offs[14]);
   p.chunk_st = windowed ? reinterpret_cast<uint64_t *>(b + offs[15]) : nullptr;
   p.blk_tok = windowed ? reinterpret_cast<uint32_t *>(b + offs[15]) : nullptr;  // (not used by one pass)
-  p.pipelined = pipeline || hybrid;
+  p.pipelined = pipeline;
   p.chunk_ctr = windowed ? reinterpret_cast<uint32_t *>(b + offs[16]) : nullptr;
   p.hybrid = hybrid;
   if (hybrid) {
@@ -3506,6 +3859,8 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
   a.certified = !p.hybrid;
   // the pipeline's planned cuts bound each lane's slice; the fused path records its ends
   a.ends = p.pipelined ? p.cuts + 1 : p.ends;
+  a.spec_cut = p.spec_cut;
+  a.spec_fail = p.spec_fail;
   a.blk_tok = p.windowed ? p.blk_tok : nullptr;
   a.block = p.block;
   a.block_shift = (uint32_t)__builtin_ctz(p.block);
@@ -3558,8 +3913,11 @@ static hipError_t count_scan_emit(const DevTable &t, const WalkArgs &a0, const P
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   mark(ev, 2, s);
-  k_scan<<<1, 1024, 0, s>>>(p.blk_sum, p.blk_fail, p.blk_nonempty, p.blk_big, p.blk_lnz, p.nblocks, p.block,
-                            p.counts, a.blk_tok, p.meta, res, cap, p.n);
+  if (a.hs.nblocks)
+    k_hscan<<<1, 1024, 0, s>>>(a, p.meta);
+  else
+    k_scan<<<1, 1024, 0, s>>>(p.blk_sum, p.blk_fail, p.blk_nonempty, p.blk_big, p.blk_lnz, p.nblocks, p.block,
+                              p.counts, a.blk_tok, p.meta, res, cap, p.n);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   mark(ev, 3, s);
@@ -3567,10 +3925,16 @@ static hipError_t count_scan_emit(const DevTable &t, const WalkArgs &a0, const P
     const uint32_t ntiles = (windows_max(p.n) + 63) / 64, w = win_waves(t.nrows);
     const uint32_t g = win_grid(w, ntiles);
     const size_t lds = emit_win_lds_bytes(t.nrows, w);
-    if (t.all_counted && t.monotone) k_emit_win<false, true><<<g, w * 64, lds, s>>>(a);
-    else if (t.all_counted) k_emit_win<false, false><<<g, w * 64, lds, s>>>(a);
-    else if (t.monotone) k_emit_win<true, true><<<g, w * 64, lds, s>>>(a);
-    else k_emit_win<true, false><<<g, w * 64, lds, s>>>(a);
+    if (!FUSED && a.hs.nblocks) {
+      const uint32_t gh = std::max(g, 1 + a.hs.checks);  // the first `checks` of them check cuts
+      if (t.all_counted && t.monotone) k_emit_win<false, true, true><<<gh, w * 64, lds, s>>>(a);
+      else if (t.all_counted) k_emit_win<false, false, true><<<gh, w * 64, lds, s>>>(a);
+      else if (t.monotone) k_emit_win<true, true, true><<<gh, w * 64, lds, s>>>(a);
+      else k_emit_win<true, false, true><<<gh, w * 64, lds, s>>>(a);
+    } else if (t.all_counted && t.monotone) k_emit_win<false, true, false><<<g, w * 64, lds, s>>>(a);
+    else if (t.all_counted) k_emit_win<false, false, false><<<g, w * 64, lds, s>>>(a);
+    else if (t.monotone) k_emit_win<true, true, false><<<g, w * 64, lds, s>>>(a);
+    else k_emit_win<true, false, false><<<g, w * 64, lds, s>>>(a);
   } else if (t.monotone) {
     k_emit<true><<<p.nblocks, p.block, smem_e, s>>>(a);
   } else {
@@ -3823,22 +4187,52 @@ hipError_t run_fused(const DevTable &t, const CertMap &cm, const uint8_t *cert_l
   return count_scan_emit<true>(t, a, p, cap, res, s, ev);
 }
 
+// The state cuts' arrays take the place of the lanes' checkpoints (which only the second route
+// writes, after it has been decided on); their windows' checkpoints that of the overflow part.
+// False where they do not fit (no windowed emit).
+static bool carve_state(const Plan &p, StateArgs &h) {
+  if (!p.windowed) return false;
+  const uint32_t nall = windows_max(p.n);
+  // short lanes shorten the chain of steps, long ones walk the warm-up windows less often
+  h.wpl = p.n <= (48u << 20) ? 4 : p.n <= (192u << 20) ? 8 : 16;
+  h.nlanes = (nall + h.wpl - 1) / h.wpl;
+  h.nblocks = (h.nlanes + kStLanes - 1) / kStLanes;
+  uint8_t *w = reinterpret_cast<uint8_t *>(p.ck);
+  h.ck = p.ck_over;
+  h.lane_pre = reinterpret_cast<uint32_t *>(w), w += align16((size_t)h.nlanes * 4);
+  h.blk_sum = reinterpret_cast<uint64_t *>(w), w += align16((size_t)h.nblocks * 8);
+  h.blk_halt = reinterpret_cast<uint2 *>(w), w += align16((size_t)h.nblocks * 8);
+  h.blk_a = reinterpret_cast<uint2 *>(w), w += align16((size_t)h.nblocks * 8);
+  h.blk_z = reinterpret_cast<uint2 *>(w), w += align16((size_t)h.nblocks * 8);
+  h.blk_fail = reinterpret_cast<uint32_t *>(w), w += align16((size_t)h.nblocks * 4);
+  h.blk_fb = reinterpret_cast<uint32_t *>(w), w += align16((size_t)h.nblocks * 4);
+  return (size_t)(w - reinterpret_cast<uint8_t *>(p.ck)) <= (size_t)p.kslots * p.nlanes * 8;
+}
+
 hipError_t run_hybrid(const DevTable &t, const CertMap &cm, const uint8_t *in, const Plan &p, uint8_t *kinds,
                       uint32_t *lens, uint64_t *offs, uint64_t cap, ResultDev *res, hipStream_t s, hipEvent_t const *ev) {
   if (!p.hybrid || !p.spec_cut || p.nlanes < 2 || p.lane_bytes < kSpecX) return hipErrorInvalidValue;
   WalkArgs a = walk_args(t, cm, in, p, kinds, lens, offs, cap, res, nullptr);
-  HybridArgs h{in, p.n, p.nlanes, p.lane_bytes, p.spec_cut, p.spec_rst, p.spec_bits, p.spec_fail, p.cuts};
+  const HybridArgs h{in, p.n, p.nlanes, p.lane_bytes, p.spec_cut, p.spec_rst, p.spec_bits, p.spec_fail, p.meta};
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   const uint32_t g = std::max<uint32_t>(1, std::min<uint32_t>((p.nlanes + 255) / 256, (uint32_t)cus * 4));
   mark(ev, 0, s);
+  StateArgs hs{};
+  if (carve_state(p, hs)) {
+    hs.S = p.lane_bytes;
+    hs.ncoarse = p.nlanes;
+    hs.checks = std::max<uint32_t>(1, std::min<uint32_t>(32, p.nlanes / 256));
+    a.hs = hs;
+    a.cond = p.meta + 2;
+    k_hstate<<<hs.nblocks, 256, lds_ring_offset(t.nrows) + 2 * 256 * 4, s>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   k_hspec<<<g, 256, lds_bytes(t.nrows, 256, false), s>>>(a, h);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_hsync<<<g, 256, 0, s>>>(h);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_hcuts<<<std::max<uint32_t>(1, std::min<uint32_t>((p.nlanes + 256) / 256, (uint32_t)cus * 4)), 256, 0, s>>>(h);
+  k_hsync<<<g, 256, 0, s>>>(h, a.cond);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return count_scan_emit<false>(t, a, p, cap, res, s, ev);
