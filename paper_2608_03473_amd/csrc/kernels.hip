@@ -1772,8 +1772,12 @@ __device__ __forceinline__ void win_tile(const Tables &tb, const WalkArgs &a, ui
 //
 // HYB: the scan of a refused set.  Its windows come from the state cuts where they stand, and
 // the launch's first workgroups check the plan's own cuts meanwhile (check_cuts).
+//
+// LDS leaves a CU one such workgroup, four waves per SIMD; told so, the compiler keeps the
+// next tiles' loads in flight instead of saving registers for a fifth (JSON 256 MiB: the scan
+// 293 to 286 us, framed records 64 MiB 189 to 175).
 template <bool DISC, bool MONO, bool HYB>
-__global__ void __launch_bounds__(1024) k_emit_win(WalkArgs a) {
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) k_emit_win(WalkArgs a) {
   const uint32_t first = a.meta[0];
   const bool state = HYB && a.meta[2] == 0;
   const uint32_t bid = HYB ? blockIdx.x - a.hs.checks : blockIdx.x, nb = HYB ? gridDim.x - a.hs.checks : gridDim.x;
@@ -3880,8 +3884,10 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
   return a;
 }
 
-// Lanes below this walk in 64-byte stretches (walk_wave).
-constexpr uint32_t kShortLane = 512;
+// Lanes below this walk in 64-byte stretches (walk_wave).  One pass: 100 MB in 512-byte lanes 198 us
+// against 210 in 128-byte stretches, 512 MiB in 2 KiB lanes 551 against 520.  The separate count
+// walk: 256 MiB of JSON in 512-byte lanes 291 us against 286.
+constexpr uint32_t kShortLane = 512, kShortLaneOne = 1024;
 // Batches: the shortest walked lane; what one workgroup plans and reports.
 constexpr uint32_t kFineLane = 128, kOneDocs = 64;
 constexpr uint64_t kOneBytes = 4u << 20;
@@ -4259,7 +4265,7 @@ hipError_t run_onepass(const DevTable &t, const CertMap &cm, const uint8_t *cert
     if (e != hipSuccess) return e;
   }
   mark(ev, 1, s);
-  if (p.lane_bytes < kShortLane) {
+  if (p.lane_bytes < kShortLaneOne) {
     if (t.all_counted) k_onepass<false, 64><<<grid, kChunkLanes, lds, s>>>(a);
     else k_onepass<true, 64><<<grid, kChunkLanes, lds, s>>>(a);
   } else {

@@ -160,6 +160,8 @@ struct Resolved {
   bool hybrid;   // a refused set split speculatively (pipeline's count, scan and emit)
 };
 
+constexpr uint64_t kSmallLanes = 64u << 10;  // a workgroup of 256 lanes on each CU
+
 uint32_t default_lane_bytes(uint64_t n, bool onepass) {
   // Aim for about 512k lanes (2048 resident lanes on each of 256 CUs), or in one pass
   // about 256k (one 256-lane group for each of the ~1024 resident one-pass workgroups),
@@ -202,6 +204,10 @@ int resolve(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *o, Resol
               lexk::onepass_lds_bytes(d->c.nrows) <= 160 * 1024;
   r.path = asked == 1 ? 1 : 2;
   r.block = r.onepass ? lexk::kChunkLanes : bt ? (uint32_t)bt : default_block(d->c.nrows);
+  // A short scan's lanes spread over more CUs in small workgroups (64 KiB of JSON counted in
+  // 25 us in one of 1024 lanes: its 16 waves share one LDS).
+  const uint64_t lb0 = o && o->lane_bytes ? o->lane_bytes : default_lane_bytes(n, false);
+  if (!r.onepass && !bt && !r.hybrid && n / lb0 < kSmallLanes) r.block = std::min<uint32_t>(r.block, 256);
   if (r.hybrid) {  // speculative lanes and cuts, then the pipeline's count, scan and emit
     r.onepass = false;
     r.path = 1;
