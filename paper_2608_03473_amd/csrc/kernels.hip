@@ -2548,33 +2548,31 @@ __global__ void __launch_bounds__(1024) k_bplan_one(BatchArgs a) {
 // restarting one byte further on after a halt (a halt at the start of a token that cannot
 // be matched), so the walk never stops.  Token starts in [b, b + kSpecX) go to head, those
 // in [b2, b2 + kSpecX) to tail (bit i: position base + i); rst: the last restart position
-// or kNone.  Token starts come in increasing order, so each bitmap is built a word at a
-// time.  Bytes are read through a 16-byte block held in registers.
+// or kNone.  Token starts come in increasing order, so each bitmap is built four words at a
+// time (a store of each word kept the block loads behind it waiting).  Bytes are read through a 16-byte block held in registers.
 template <bool MONO>
 __device__ void walk_spec(const Tables &tb, const uint8_t *in, uint32_t n, uint32_t b, uint32_t end, uint32_t b2,
                           uint32_t *head, uint32_t *tail, uint32_t &rst) {
-  uint32_t hw = 0, hv = 0, tw = 0, tv = 0;  // current word index and bits of head and tail
-  auto mark = [&](uint32_t t) {
-    if (t - b < kSpecX) {
-      const uint32_t w = (t - b) >> 5;
-      if (w != hw) {
-        head[hw] = hv;
-        hw = w;
-        hv = 0;
-      }
-      hv |= 1u << ((t - b) & 31);
+  uint4 hv = make_uint4(0, 0, 0, 0), tv = hv;  // the current four words of head and tail
+  uint32_t hg = 0, tg = 0;                     // and their place, in fours
+  auto set = [](uint32_t word, uint32_t bits, uint32_t *words, uint32_t &g, uint4 &v) {
+    if ((word >> 2) != g) {
+      reinterpret_cast<uint4 *>(words)[g] = v;
+      g = word >> 2;
+      v = make_uint4(0, 0, 0, 0);
     }
-    if (t - b2 < kSpecX) {
-      const uint32_t w = (t - b2) >> 5;
-      if (w != tw) {
-        tail[tw] = tv;
-        tw = w;
-        tv = 0;
-      }
-      tv |= 1u << ((t - b2) & 31);
-    }
+    const uint32_t q = word & 3;
+    v.x |= q == 0 ? bits : 0;
+    v.y |= q == 1 ? bits : 0;
+    v.z |= q == 2 ? bits : 0;
+    v.w |= q == 3 ? bits : 0;
   };
-  for (uint32_t w = 0; w < kSpecWords; ++w) head[w] = tail[w] = 0;
+  auto mark = [&](uint32_t t) {
+    if (t - b < kSpecX) set((t - b) >> 5, 1u << ((t - b) & 31), head, hg, hv);
+    if (t - b2 < kSpecX) set((t - b2) >> 5, 1u << ((t - b2) & 31), tail, tg, tv);
+  };
+  for (uint32_t w = 0; w < kSpecWords / 4; ++w)
+    reinterpret_cast<uint4 *>(head)[w] = reinterpret_cast<uint4 *>(tail)[w] = make_uint4(0, 0, 0, 0);
   const uintptr_t base = reinterpret_cast<uintptr_t>(in);
   int64_t cb = INT64_MIN;  // position of the cached block (16-aligned in memory)
   uint4 cv = make_uint4(0, 0, 0, 0);
@@ -2589,7 +2587,7 @@ __device__ void walk_spec(const Tables &tb, const uint8_t *in, uint32_t n, uint3
   // the token starts of one aligned 16-byte block (bit k: position P + k) into both bitmaps,
   // a word at a time (positions come in increasing order, as for mark)
   auto mark_bits = [&](uint32_t mk, uint32_t P) {
-    auto put = [&](uint32_t bits, int64_t off, uint32_t *words, uint32_t &cw, uint32_t &cv) {
+    auto put = [&](uint32_t bits, int64_t off, uint32_t *words, uint32_t &g, uint4 &v) {
       if (off <= -16 || off >= (int64_t)kSpecX) return;
       if (off < 0) {
         bits >>= (uint32_t)(-off);
@@ -2597,22 +2595,11 @@ __device__ void walk_spec(const Tables &tb, const uint8_t *in, uint32_t n, uint3
       }
       const uint32_t wi = (uint32_t)off >> 5, sh = (uint32_t)off & 31;
       const uint32_t lo = bits << sh, hi = sh > 16 ? bits >> (32 - sh) : 0;
-      if (lo) {
-        if (wi != cw) {
-          words[cw] = cv;
-          cw = wi;
-          cv = 0;
-        }
-        cv |= lo;
-      }
-      if (hi && wi + 1 < kSpecWords) {
-        words[cw] = cv;
-        cw = wi + 1;
-        cv = hi;
-      }
+      if (lo) set(wi, lo, words, g, v);
+      if (hi && wi + 1 < kSpecWords) set(wi + 1, hi, words, g, v);
     };
-    put(mk, (int64_t)P - b, head, hw, hv);
-    put(mk, (int64_t)P - b2, tail, tw, tv);
+    put(mk, (int64_t)P - b, head, hg, hv);
+    put(mk, (int64_t)P - b2, tail, tg, tv);
   };
   uint32_t st = tb.start, tok = b, lacc = b, lrow = 0, lblk = b, lst0 = 0;
   // non-monotone automata: failed traces as cursors, as the lane walk's fallback keeps them
@@ -2737,8 +2724,8 @@ __device__ void walk_spec(const Tables &tb, const uint8_t *in, uint32_t n, uint3
       if (p < end) mark(p);
     }
   }
-  head[hw] = hv;
-  tail[tw] = tv;
+  reinterpret_cast<uint4 *>(head)[hg] = hv;
+  reinterpret_cast<uint4 *>(tail)[tg] = tv;
 }
 
 // The speculative walk of speculative lane i (< the batch's count of them).
@@ -2813,12 +2800,16 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
   const uint32_t rm = refused_mask(a);
   // every wave's first tile is fixed (all waves taking it from the queue at once would
   // queue on its atomic counter); later ones come from the queue, past the fixed ones
-  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6, gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  // The first tiles go around the workgroups, a wave of each in turn: the speculative ones, a
+  // 4 KiB chain each, then share their CU with shorter walks, not with 15 of their own kind.
+  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6, gw = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
   const bool queued = nst + (nlanes + 63) / 64 > nwaves;
   for (uint32_t tile = gw;; tile = queued ? next_tile(&a.meta[kQCount]) + nwaves : kNone) {
     if (tile < nst) {  // wave-uniform
       const uint32_t i = tile * 64 + lane;
+      __builtin_amdgcn_s_setprio(3);  // the pass waits for the longest chains
       if (i < nspec) spec_lane(a, l, i);
+      __builtin_amdgcn_s_setprio(0);
       continue;
     }
     const uint32_t t = tile - nst;
