@@ -3489,7 +3489,7 @@ __global__ void __launch_bounds__(256) k_hstate(WalkArgs a) {
     st = k ? s2 : st;
     tok = k ? t2 : tok;
   }
-  // walks the lane from (st, tok), recording every window's checkpoint
+  // walks the lane from (st, tok), recording its windows' checkpoints
   auto run = [&](bool act) {
     cnt = act ? 0 : cnt;
     for (uint32_t w = 0; w < wpl; ++w) {
@@ -3497,7 +3497,8 @@ __global__ void __launch_bounds__(256) k_hstate(WalkArgs a) {
       const bool mine = act && i < i1;
       const Win64 cur = dat;
       if (act && i + 1 < i1) dat = load(i + 1);
-      if (mine) a.hs.ck[i] = make_uint2(((st >> kRowShift) << 24) | cnt, tok);
+      // (own lanes only: a warm-up lane is another workgroup's, and may have guessed wrong)
+      if (mine && own) a.hs.ck[i] = make_uint2(((st >> kRowShift) << 24) | cnt, tok);
       uint32_t s2 = st, t2 = tok, c2 = cnt;
       if (__all(!mine || inside(i))) state_window<false, false>(tb, cur, wpos(i), a.n, s2, t2, c2);
       else state_window<true, false>(tb, cur, wpos(i), a.n, s2, t2, c2);
