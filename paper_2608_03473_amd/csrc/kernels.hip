@@ -840,6 +840,8 @@ __device__ __forceinline__ bool walk_wave(LaneState &L, const Tables &tb, const 
     const int er = mine ? (int)min<int64_t>(LINE + 1, (int64_t)e - P) : -1;
     const int lo = max(0, sr), hi = (int)max<int64_t>(0, min<int64_t>(LINE, (int64_t)lim - P));
     const int keep = er + (mine && e < lim);
+    // (a batch that stands its windowed emit down has no checkpoints to write: ck.main is null)
+    const int cs = CK && ck.main ? sr : LINE;
     const uint32_t st0 = L.st;
     stl = mine ? st0 : stl;
     uint32_t st = L.st;
@@ -857,7 +859,7 @@ __device__ __forceinline__ bool walk_wave(LaneState &L, const Tables &tb, const 
     // leaves in one 16-byte store when it fills one block of ck_index)
     auto checkpoint = [&](int i) {
       if (!CK || i % 4) return;
-      const bool in_s = 16 * i > sr && 16 * i < er;
+      const bool in_s = 16 * i > cs && 16 * i < er;
       L.st = st & kRowMask;
       if (LINE == 64) {
         if (in_s) ck_record(ck, L, blk);
