@@ -1522,27 +1522,54 @@ __device__ __forceinline__ WinMeta state_meta(const WalkArgs &a, uint32_t i, uin
 // here from the state cuts) and of a walk begun at k S, as walk_spec runs it; without one it
 // takes the text as one slice, or, at the last lane, one slice less.  Only the reported number of
 // slices depends on it.  Both scans are the same from such a position on, so they have one
-// before a window's start (or the text's end) exactly when they are there in the same row and
-// token: only the second walk is run, against the windows' checkpoints, in 16-byte blocks (most
-// boundaries agree at the first or second window; comparing the two token by token took 490 us
-// for 32 MiB, several times the emit beside it).
+// before a window's start exactly when they are there in the same row and token: only the second
+// walk is run, against the windows' checkpoints, in 16-byte blocks (most boundaries agree at the
+// first or second window; comparing the two token by token took 490 us for 32 MiB, several times
+// the emit beside it).  The window that the interval ends in is the exception, for its end is no
+// window start (the buffer's alignment, a lane of any multiple of 16, the text's end): there the
+// token starts of both are compared, the serial scan's as a mask (start_mask).
+
+// The serial scan's token starts in window i (bit b: byte b of the window) before position end.
+__device__ __forceinline__ uint64_t start_mask(const WalkArgs &a, const Tables &tb, uint32_t i, uint32_t mis0,
+                                               uint32_t end) {
+  const uint32_t w0 = i * kWin - mis0;
+  uint32_t st = row_state(a.hs.ck[i].x >> 24);
+  uint64_t starts = 0;
+  for (uint32_t q = 0; q < kWin && w0 + q < end; q += 16) {
+    const uint4 v = load_block(a.in, w0 + q, a.n);
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      st = entry_from(tb, st, byte_of(v, k));
+      m |= ((st >> 1) & 1u) << k;  // EMIT
+    }
+    starts |= (uint64_t)m << q;
+  }
+  return end - w0 < kWin ? starts & ((1ull << (end - w0)) - 1) : starts;
+}
+
 __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) {
   if (threadIdx.x >= 256) return;  // one wave per SIMD: a chain of dependent steps
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.in);
   const uint32_t mis0 = (uint32_t)(base & (kWin - 1));
-  const uint2 z = a.hs.blk_z[a.hs.nblocks - 1];  // the serial scan at the text's end
   for (uint32_t k = 1 + blockIdx.x * 256 + threadIdx.x; k < a.hs.ncoarse; k += a.hs.checks * 256) {
     const uint32_t c = k * a.hs.S, end = (uint32_t)min<uint64_t>((uint64_t)c + kSpecX, a.n);
     const uint32_t bend = (uint32_t)min<uint64_t>((uint64_t)c + a.hs.S + kSpecX, a.n);  // the walk's end
+    const uint32_t iw = (uint32_t)(((uint64_t)end - 1 + mis0) / kWin), w0 = iw * kWin - mis0;  // the last window
     uint32_t st = tb.start, p = c, tok = c, lacc = c;
-    bool same = false;
+    uint64_t starts = 0;
+    bool known = false, same = false;
+    // a token start of the second walk: of the serial scan too, in the last window?
+    auto start = [&](uint32_t x) {
+      if (x < w0 || x >= end) return;
+      if (!known) starts = start_mask(a, tb, iw, mis0, end);
+      known = true;
+      same = same || ((starts >> (x - w0)) & 1);
+    };
+    start(c);
     int64_t nb = INT64_MIN;  // position of the block loaded ahead
     uint4 nv = make_uint4(0, 0, 0, 0);
-    while (tok < end) {
-      if (p >= bend) {
-        same = bend == a.n && st == z.x && tok == z.y;
-        break;
-      }
+    while (!same && tok < end && p < bend) {
       const uint32_t lo = (uint32_t)((base + p) & 15);
       const int64_t blk = (int64_t)p - lo;
       const uint32_t hi = (uint32_t)min<int64_t>(16, (int64_t)bend - blk);
@@ -1563,17 +1590,17 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) 
       const uint32_t me = m & 0xAAAAAAAAu;
       tok = me ? (uint32_t)blk + ((31 - __clz(me)) >> 1) : tok;
       lacc = ac ? (uint32_t)blk + (31 - __clz(ac)) - 15 : lacc;
+      if (blk + 16 > (int64_t)w0)
+        for (uint32_t x = me; x && !same; x &= x - 1) start((uint32_t)blk + ((uint32_t)(__ffs(x) - 1) >> 1));
       p = (uint32_t)(blk + hi);
       if (st == tb.sink || st == tb.fail) {  // restart, as walk_spec does
         p = tok = st == tb.fail && tb.fail != tb.sink && lacc > tok ? lacc : tok + 1;
         lacc = p;
         st = tb.start;
-      } else if (p < a.n && ((base + p) & (kWin - 1)) == 0) {
+        start(p);
+      } else if (p <= w0 && ((base + p) & (kWin - 1)) == 0) {
         const uint2 w = a.hs.ck[(p + (uint64_t)mis0) / kWin];
-        if (row_state(w.x >> 24) == st && w.y == tok && tok < end) {
-          same = true;
-          break;
-        }
+        same = row_state(w.x >> 24) == st && w.y == tok;
       }
     }
     if (!same) atomicMin(&a.res->nslices, k + 1 == a.hs.ncoarse ? a.hs.ncoarse - 1 : 1u);
