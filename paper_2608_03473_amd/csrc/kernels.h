@@ -45,7 +45,9 @@ struct Plan {
   uint32_t *blk_fail;      // nblocks: first halted lane of the block or ~0u
   uint32_t *blk_nonempty;  // nblocks
   uint32_t *blk_big;       // nblocks: a slice of 2^24 bytes or more (no checkpoints)
-  uint32_t *meta;          // [0] = first halted lane or ~0u, [1] = checkpoints unusable
+  // [0] = first halted lane or ~0u, [1] = checkpoints unusable; hybrid plan: [2] = its second
+  // route, [3] = how check_cuts runs
+  uint32_t *meta;
   uint32_t *lane_pre;      // nlanes: exclusive prefix of counts inside the workgroup
   // Windowed emit (monotone automata whose token ends are all counted): the count walk
   // records its state at every 64-byte-aligned address strictly inside a slice; the emit

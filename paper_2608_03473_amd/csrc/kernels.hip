@@ -948,7 +948,7 @@ struct StateArgs {
   uint64_t *blk_sum;              // nblocks: counts (k_hstate), their exclusive prefix (k_hscan)
   uint32_t *blk_fail;             // first halted lane or ~0u
   uint2 *blk_halt;                // its failed token's start, its block's tokens up to the halt
-  uint32_t *blk_fb;               // some lane fell back
+  uint32_t *blk_fb;               // bit 0: some lane fell back; bit 1: the halt is the text's end
   uint2 *blk_a, *blk_z;           // row and token start at the first own lane's start, the last's end
 };
 
@@ -1529,26 +1529,34 @@ __device__ __forceinline__ WinMeta state_meta(const WalkArgs &a, uint32_t i, uin
 // window start (the buffer's alignment, a lane of any multiple of 16, the text's end): there the
 // token starts of both are compared, the serial scan's as a mask (start_mask).
 
-// The serial scan's token starts in window i (bit b: byte b of the window) before position end.
+// The serial scan's token starts in window i (bit b: byte b of the window) before position end, and
+// its row at end.
 __device__ __forceinline__ uint64_t start_mask(const WalkArgs &a, const Tables &tb, uint32_t i, uint32_t mis0,
-                                               uint32_t end) {
+                                               uint32_t end, uint32_t &st) {
   const uint32_t w0 = i * kWin - mis0;
-  uint32_t st = row_state(a.hs.ck[i].x >> 24);
+  st = row_state(a.hs.ck[i].x >> 24);
   uint64_t starts = 0;
   for (uint32_t q = 0; q < kWin && w0 + q < end; q += 16) {
     const uint4 v = load_block(a.in, w0 + q, a.n);
     uint32_t m = 0;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-      st = entry_from(tb, st, byte_of(v, k));
-      m |= ((st >> 1) & 1u) << k;  // EMIT
+      const uint32_t y = entry_from(tb, st, byte_of(v, k));
+      const bool in = w0 + q + k < end;
+      st = in ? y : st;
+      m |= in ? ((y >> 1) & 1u) << k : 0;  // EMIT
     }
     starts |= (uint64_t)m << q;
   }
-  return end - w0 < kWin ? starts & ((1ull << (end - w0)) - 1) : starts;
+  st &= kRowMask;
+  return starts;
 }
 
-__device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) {
+// halts: the scan halts past the last lane's interval, as far as its first halted state lane tells.
+// It does so exactly when its row at the interval's end is alive; the walk of the lane before the
+// last then ends without meeting the halt, and the plan stands (with one slice less) if the last
+// boundary finds no cut and the others do.
+__device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb, bool halts) {
   if (threadIdx.x >= 256) return;  // one wave per SIMD: a chain of dependent steps
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.in);
   const uint32_t mis0 = (uint32_t)(base & (kWin - 1));
@@ -1556,13 +1564,13 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) 
     const uint32_t c = k * a.hs.S, end = (uint32_t)min<uint64_t>((uint64_t)c + kSpecX, a.n);
     const uint32_t bend = (uint32_t)min<uint64_t>((uint64_t)c + a.hs.S + kSpecX, a.n);  // the walk's end
     const uint32_t iw = (uint32_t)(((uint64_t)end - 1 + mis0) / kWin), w0 = iw * kWin - mis0;  // the last window
-    uint32_t st = tb.start, p = c, tok = c, lacc = c;
+    uint32_t st = tb.start, p = c, tok = c, lacc = c, at_end = 0;
     uint64_t starts = 0;
     bool known = false, same = false;
     // a token start of the second walk: of the serial scan too, in the last window?
     auto start = [&](uint32_t x) {
       if (x < w0 || x >= end) return;
-      if (!known) starts = start_mask(a, tb, iw, mis0, end);
+      if (!known) starts = start_mask(a, tb, iw, mis0, end, at_end);
       known = true;
       same = same || ((starts >> (x - w0)) & 1);
     };
@@ -1603,7 +1611,13 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb) 
         same = row_state(w.x >> 24) == st && w.y == tok;
       }
     }
-    if (!same) atomicMin(&a.res->nslices, k + 1 == a.hs.ncoarse ? a.hs.ncoarse - 1 : 1u);
+    const bool last = k + 1 == a.hs.ncoarse;
+    if (last && halts) {  // a cut there, or a halt before the interval's end, and the plan falls back
+      if (!known) (void)start_mask(a, tb, iw, mis0, end, at_end);
+      if (same || at_end == tb.sink || at_end == tb.fail) atomicMin(&a.res->nslices, 1u);
+    } else if (!same) {
+      atomicMin(&a.res->nslices, last ? a.hs.ncoarse - 1 : 1u);
+    }
   }
 }
 
@@ -1838,10 +1852,10 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
   const uint32_t bid = HYB ? blockIdx.x - a.hs.checks : blockIdx.x, nb = HYB ? gridDim.x - a.hs.checks : gridDim.x;
   const Lds l = carve_lds(a.nrows);
   if (HYB && blockIdx.x < a.hs.checks) {  // uniform
-    if (!state || first != kNone || a.n == 0) return;
+    if (!state || a.meta[3] == 0 || a.n == 0) return;
     stage_tables(a, l, false);
     const Tables tb{lds_bytes_of(l.T), l.info, l.kind, a.sink, a.fail, 0};
-    check_cuts(a, tb);
+    check_cuts(a, tb, a.meta[3] == 2);
     return;
   }
   if (a.meta[1] != 0) {  // uniform
@@ -3591,11 +3605,11 @@ __global__ void __launch_bounds__(256) k_hstate(WalkArgs a) {
     }
   }
   // the text's end, halts and fallbacks of own lanes (those past the first halt do not count)
-  bool halted = own && st == tb.sink, fell = own && st == tb.fail && tb.fail != tb.sink;
+  bool halted = own && st == tb.sink, fell = own && st == tb.fail && tb.fail != tb.sink, open = false;
   if (own && i0 < nall && i1 == nall && !dead(st) && st != tb.start) {
     const uint32_t row = st >> kRowShift;
     if (tb.info[row] & kInfoAcc) cnt += tb.info[row] & kInfoCount ? 1 : 0;
-    else if (tb.fail == tb.sink) halted = true;
+    else if (tb.fail == tb.sink) halted = open = true;  // the text ends inside a token
     else fell = true;
   }
   const uint32_t mine = own ? cnt : 0;
@@ -3617,8 +3631,8 @@ __global__ void __launch_bounds__(256) k_hstate(WalkArgs a) {
     F = min(F, l.red32[4 + w]);
   }
   if (own) a.hs.lane_pre[k] = pre + incl - mine;
-  const bool fb = __any(fell && k < F);
-  if (lane == 0) l.red32[8 + wid] = fb;
+  const bool fb = __any(fell && k < F), op = __any(open && k == F);
+  if (lane == 0) l.red32[8 + wid] = (fb ? 1u : 0u) | (op ? 2u : 0u);
   if (own && k == F) a.hs.blk_halt[blockIdx.x] = make_uint2(tok, pre + incl);
   if (tid == kStWarm) a.hs.blk_a[blockIdx.x] = make_uint2(as, at);
   if (own && (tid == 255 || k + 1 == a.hs.nlanes)) a.hs.blk_z[blockIdx.x] = make_uint2(st, tok);
@@ -3640,7 +3654,7 @@ __device__ __forceinline__ bool state_stands(const StateArgs &h, uint32_t *red, 
   for (uint32_t i = threadIdx.x; i < h.nblocks; i += blockDim.x) {
     f = min(f, h.blk_fail[i]);
     const uint2 x = h.blk_a[i], y = i ? h.blk_z[i - 1] : x;
-    if (h.blk_fb[i] || x.x != y.x || x.y != y.y) bad = min(bad, i);
+    if ((h.blk_fb[i] & 1) || x.x != y.x || x.y != y.y) bad = min(bad, i);
   }
   for (int d = 32; d; d >>= 1) {
     f = min(f, (uint32_t)__shfl_xor((int)f, d));
@@ -3701,7 +3715,20 @@ __global__ void __launch_bounds__(1024) k_hscan(WalkArgs a, uint32_t *__restrict
     a.res->ntokens = ntok;
     a.res->error_offset = halt.x;
     a.res->status = ntok > a.cap ? -4 : 0;
-    a.res->nslices = f == kNone ? h.ncoarse : 1;  // a halt makes the plan fall back
+    // The slices, before check_cuts (meta[3]: not to run; 1: to run; 2: to run for a halt).  A halt
+    // inside the text makes the plan fall back, for the lane that meets it restarts there; but no
+    // lane does when it lies past the last sync window and the last lane has no cut (see check_cuts).
+    // A text that ends inside a token restarts no lane.
+    uint32_t ns = h.ncoarse, check = 1;
+    if (f != kNone && !(h.blk_fb[b] & 2)) {
+      const uint64_t e0 = (uint64_t)(h.ncoarse - 1) * h.S + kSpecX;
+      const uint32_t mis0 = (uint32_t)(reinterpret_cast<uintptr_t>(a.in) & (kWin - 1));
+      const bool past = e0 < a.n && (e0 - 1 + mis0) / kWin / h.wpl <= f;
+      ns = past ? h.ncoarse - 1 : 1;
+      check = past ? 2 : 0;
+    }
+    meta[3] = check;
+    a.res->nslices = ns;
   }
 }
 

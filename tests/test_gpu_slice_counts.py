@@ -47,6 +47,33 @@ def check(name, buf, mode, pads=(0,), lane=S):
     return want
 
 
+@pytest.mark.parametrize("name,mode,tail", [("clike_d", 0, b'"ab'), ("clike_d", 0, b"\x01"), ("json", 0, b'"ab'),
+                                            ("clike_b", 0, b"/* a b"), ("clike_b", 1, b'"ab')])
+def test_halt_at_the_end(name, mode, tail):
+    """An unterminated last token halts the scan without a restart in any speculative lane."""
+    for n in (8192, 12_300, 40_000):
+        w = workloads.json(n, n) if name == "json" else workloads.clike(n, n, bcomment=name == "clike_b")
+        w = np.concatenate([w[: n - len(tail)], np.frombuffer(tail, np.uint8)])
+        print(f"[case] {name} mode={mode} n={n} tail={tail}", flush=True)
+        want = check(name, w, mode, pads=(0, 5))
+        if name == "clike_d" and tail == b'"ab':
+            assert want > 1
+
+
+def test_halt_past_the_last_window():
+    """A string over the last lane's sync window that halts after it: no lane restarts past its cut,
+    so the plan keeps its other cuts; one that halts inside the window falls back."""
+    base = workloads.clike(9000, 5)
+    base[base == ord('"')] = ord("x")
+    for at, size in ((8192 - 100, 2300), (8192 - 100, 2100), (8192 - 100, 700), (8192 + 300, 2300), (4000, 6600)):
+        w = np.concatenate([base[:at], np.frombuffer(b'\n"' + b"x" * size + b"\n", np.uint8)])
+        w = np.concatenate([w, workloads.clike(12_000 - w.size, 6)])
+        print(f"[case] string of {size} at {at}", flush=True)
+        want = check("clike_d", w, 0, pads=(0, 1, 63))
+        if (at, size) == (8192 - 100, 2300):
+            assert want == 2
+
+
 @pytest.mark.parametrize("lane", [S, S + 16, S + 48])
 @pytest.mark.parametrize("d", [1960, 1985, 2000, 2020, 2046, 2047, 2048, 2049])
 def test_first_common_start_late_in_the_window(d, lane):
