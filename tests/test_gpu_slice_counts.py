@@ -63,11 +63,10 @@ def test_halt_at_the_end(name, mode, tail):
 def test_halt_past_the_last_window():
     """A string over the last lane's sync window that halts after it: no lane restarts past its cut,
     so the plan keeps its other cuts; one that halts inside the window falls back."""
-    base = workloads.clike(9000, 5)
-    base[base == ord('"')] = ord("x")
+    base = np.frombuffer(b"if (a1 <= 20) b = c + 7;\n\tdd = 'e';\n".replace(b"'", b" ") * 300, np.uint8)  # no halt of its own
     for at, size in ((8192 - 100, 2300), (8192 - 100, 2100), (8192 - 100, 700), (8192 + 300, 2300), (4000, 6600)):
         w = np.concatenate([base[:at], np.frombuffer(b'\n"' + b"x" * size + b"\n", np.uint8)])
-        w = np.concatenate([w, workloads.clike(12_000 - w.size, 6)])
+        w = np.concatenate([w, base[: 12_000 - w.size]])
         print(f"[case] string of {size} at {at}", flush=True)
         want = check("clike_d", w, 0, pads=(0, 1, 63))
         if (at, size) == (8192 - 100, 2300):
