@@ -2275,9 +2275,9 @@ struct DocResDev {  // mirrors lex_doc_result
 };
 
 // meta words: work queues (count, lane emit), lane / speculative-lane / tile totals, a stopped batch, no windowed emit for this batch,
-// some document for the lane emit
+// some document for the lane emit, the lane that is walked
 enum { kQCount = 0, kQEmit = 1, kNLanes = 2, kBad = 3, kNSpec = 4, kNTiles = 6, kNoWin = 7,
-       kAnyLane = 8, kBatchMeta = 16 };
+       kAnyLane = 8, kFine = 9, kBatchMeta = 16 };
 
 struct BatchArgs {
   const uint32_t *table;
@@ -2288,9 +2288,11 @@ struct BatchArgs {
   const uint8_t *bytes;
   uint64_t nbytes;
   const DocDev *docs;
-  // lane_bytes: the plan's lane, which slices are counted by; fine_bytes: the lane that is walked
-  // (lane_bytes over a power of two: a small batch has too few lanes of its own to fill the chip)
-  uint32_t ndocs, lane_bytes, fine_bytes, max_lanes;
+  // lane_bytes: the plan's lane, which slices are counted by; fine_bytes: the lane to walk
+  // (lane_bytes over a power of two: a small batch has too few lanes of its own to fill the chip).
+  // Documents that share bytes may have more walked lanes than the workspace's max_lanes; they are
+  // then walked in the plan's (meta[kFine]), of which plan_lanes are accepted.
+  uint32_t ndocs, lane_bytes, fine_bytes, max_lanes, plan_lanes;
   uint32_t *meta;  // kBatchMeta words: queues, lane count
   uint64_t *part;  // kDocGroups x kPartWords: per-group sums of the planning and result kernels
   uint32_t *lanes_of, *lane_base, *lane_doc, *cuts, *ends, *counts, *halted, *lane_pre, *doc_halt;
@@ -2377,17 +2379,18 @@ __device__ __forceinline__ bool spec_split(const BatchArgs &a, uint32_t rm, cons
   return d.inst < a.ninst && ((rm >> d.inst) & 1) && !(d.flags & 1) && d.length > max(a.spec_bytes, a.lane_bytes);
 }
 
-__device__ __forceinline__ bool one_lane(const BatchArgs &a, uint32_t rm, const DocDev &d) {
+__device__ __forceinline__ bool one_lane(const BatchArgs &a, uint32_t rm, const DocDev &d, uint32_t lane_bytes) {
   // (an unknown instance stops the batch)
   return !spec_split(a, rm, d) &&
-         (d.length <= a.fine_bytes || (d.flags & 1) || d.inst >= a.ninst || ((rm >> d.inst) & 1));
+         (d.length <= lane_bytes || (d.flags & 1) || d.inst >= a.ninst || ((rm >> d.inst) & 1));
 }
 
 __device__ __forceinline__ uint32_t ceil_div(uint32_t x, uint32_t y) { return x / y + (x % y != 0); }
 
-__device__ __forceinline__ uint32_t doc_lanes(const BatchArgs &a, uint32_t rm, const DocDev &d) {
+// Its lanes where they are lane_bytes long (the walked or the plan's).
+__device__ __forceinline__ uint32_t doc_lanes(const BatchArgs &a, uint32_t rm, const DocDev &d, uint32_t lane_bytes) {
   if (spec_split(a, rm, d)) return ceil_div(d.length, a.spec_bytes);
-  return one_lane(a, rm, d) ? 1 : ceil_div(d.length, a.fine_bytes);
+  return one_lane(a, rm, d, lane_bytes) ? 1 : ceil_div(d.length, lane_bytes);
 }
 
 // The planning and result kernels (k_bplan_*, k_bscan_*) split the document table into at
@@ -2397,7 +2400,7 @@ __device__ __forceinline__ uint32_t doc_lanes(const BatchArgs &a, uint32_t rm, c
 // own documents.  (One workgroup for the whole table left the chip idle for 0.2 ms at
 // 50 000 documents.)
 constexpr uint32_t kDocGroups = 256;
-constexpr uint32_t kPartWords = 8;  // per group: plan sums (0-4), result sums (5-7)
+constexpr uint32_t kPartWords = 8;  // per group: plan sums (0-6), later result sums (5-7)
 
 __host__ __device__ inline uint32_t doc_groups(uint32_t ndocs) {
   return ndocs > 256u * kDocGroups ? kDocGroups : ndocs ? (ndocs + 255) / 256 : 1;
@@ -2490,8 +2493,9 @@ __device__ __forceinline__ void group_prefix(const uint64_t *part, uint32_t q0, 
 // sums (v) and whether it holds a bad record; the queues reset.  The document table is the
 // caller's device data: a document outside the bytes, an unknown instance or flag, or more
 // lanes than the workspace holds stops the batch.
-// v: single-lane long documents, other lanes, speculative lanes, tiles, bad
-__device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[5],
+// v: single-lane long documents, other lanes, speculative lanes, tiles, bad; the first two in the
+// plan's lanes
+__device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[7],
                                           uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2500,37 +2504,41 @@ __device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint3
     a.meta[kAnyLane] = 0;
   }
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  for (int q = 0; q < 5; ++q) v[q] = 0;
+  for (int q = 0; q < 7; ++q) v[q] = 0;
   for (uint32_t d = lo + threadIdx.x; d < hi; d += blockDim.x) {
     const DocDev x = a.docs[d];
     const bool fits = x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
     v[4] |= !fits || x.inst >= a.ninst || x.flags > 1;
-    const uint32_t nl = doc_lanes(a, rm, x);
-    a.lanes_of[d] = nl;
+    const uint32_t nl = doc_lanes(a, rm, x, a.fine_bytes), np = doc_lanes(a, rm, x, a.lane_bytes);
     a.spec_fail[d] = 0;
-    const bool first = nl == 1 && x.length > a.fine_bytes;
+    const bool first = nl == 1 && x.length > a.fine_bytes, firstp = np == 1 && x.length > a.lane_bytes;
     v[0] += first ? nl : 0;
     v[1] += first ? 0 : nl;
+    v[5] += firstp ? np : 0;
+    v[6] += firstp ? 0 : np;
     if (spec_split(a, rm, x)) v[2] += nl;
     if (fits) v[3] += doc_tiles(base + x.offset, x.length);
   }
-  block_sum<5>(v, red);
+  block_sum<7>(v, red);
 }
 
 // Planning, second half: lane numbering (long single-lane documents first, then the rest,
 // each in document order), speculative-lane and tile numbering, from the sums of the earlier
 // groups (pre) and of all (tot); the first group writes the totals and the stop flags.
-__device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uint32_t hi, const uint64_t (&pre)[5],
-                                            const uint64_t (&tot)[5], uint64_t (*red)[kRedWaves]) {
+__device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uint32_t hi, const uint64_t (&pre)[7],
+                                            const uint64_t (&tot)[7], uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  uint64_t r[4] = {pre[0], tot[0] + pre[1], pre[2], pre[3]};  // 64-bit: a hostile table may ask for 2^32 lanes
+  const bool fits_fine = tot[0] + tot[1] <= a.max_lanes;
+  const uint32_t fine = fits_fine ? a.fine_bytes : a.lane_bytes;
+  // 64-bit: a hostile table may ask for 2^32 lanes
+  uint64_t r[4] = {fits_fine ? pre[0] : pre[5], fits_fine ? tot[0] + pre[1] : tot[5] + pre[6], pre[2], pre[3]};
   for (uint32_t d0 = lo; d0 < hi; d0 += blockDim.x) {  // workgroup-uniform: the scans see every thread
     const uint32_t d = d0 + threadIdx.x;
     const bool in = d < hi;
     const DocDev x = a.docs[in ? d : lo];
-    const uint32_t nl = in ? doc_lanes(a, rm, x) : 0;
-    const bool first = nl == 1 && x.length > a.fine_bytes;
+    const uint32_t nl = in ? doc_lanes(a, rm, x, fine) : 0;
+    const bool first = nl == 1 && x.length > fine;
     const bool fits = in && x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
     uint64_t v[4] = {first ? nl : 0, first ? 0 : nl, in && spec_split(a, rm, x) ? nl : 0,
                      fits ? doc_tiles(base + x.offset, x.length) : 0};
@@ -2538,6 +2546,7 @@ __device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uin
     uint64_t t[4];
     block_incl<4>(v, t, red);
     if (in) {
+      a.lanes_of[d] = nl;
       const uint64_t lb = first ? r[0] + v[0] - v0[0] : r[1] + v[1] - v0[1];
       a.lane_base[d] = (uint32_t)min<uint64_t>(lb, 0xFFFFFFFFu);  // unused when stopped
       a.spec_base[d] = (uint32_t)min<uint64_t>(r[2] + v[2] - v0[2], 0xFFFFFFFFu);
@@ -2547,8 +2556,9 @@ __device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uin
     for (int q = 0; q < 4; ++q) r[q] += t[q];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const uint64_t nlanes = tot[0] + tot[1], nspec = tot[2];
-    const bool stop = tot[4] || nlanes > a.max_lanes || nspec > a.max_spec;
+    const uint64_t planned = tot[5] + tot[6], nlanes = fits_fine ? tot[0] + tot[1] : planned, nspec = tot[2];
+    const bool stop = tot[4] || planned > a.plan_lanes || nspec > a.max_spec;
+    a.meta[kFine] = fine;
     a.meta[kBad] = stop;
     a.meta[kNLanes] = stop ? 0 : (uint32_t)nlanes;
     a.meta[kNSpec] = stop ? 0 : (uint32_t)nspec;
@@ -2580,18 +2590,18 @@ __device__ __forceinline__ void map_docs(const BatchArgs &a, uint32_t wave, uint
 }
 
 __global__ void __launch_bounds__(256) k_bplan_a(BatchArgs a) {
-  __shared__ uint64_t red[5][kRedWaves];
+  __shared__ uint64_t red[7][kRedWaves];
   uint32_t lo, hi;
   group_range(a.ndocs, lo, hi);
-  uint64_t v[5];
+  uint64_t v[7];
   plan_sums(a, lo, hi, v, red);
-  if (threadIdx.x < 5) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
+  if (threadIdx.x < 7) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
 }
 
 __global__ void __launch_bounds__(256) k_bplan_b(BatchArgs a) {
-  __shared__ uint64_t red[10][kRedWaves];
-  uint64_t pre[5], tot[5];
-  group_prefix<5>(a.part, 0, pre, tot, red);
+  __shared__ uint64_t red[14][kRedWaves];
+  uint64_t pre[7], tot[7];
+  group_prefix<7>(a.part, 0, pre, tot, red);
   uint32_t lo, hi;
   group_range(a.ndocs, lo, hi);
   plan_number(a, lo, hi, pre, tot, red);
@@ -2601,12 +2611,12 @@ __global__ void __launch_bounds__(256) k_bmap(BatchArgs a) {
   map_docs(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
 }
 
-// A small batch (one_plan) in one launch of one workgroup: a launch costs 4-5 us here, more
-// than the planning of a few hundred documents.
+// A small batch (at most kOneDocs documents and kOneBytes bytes) in one launch of one workgroup:
+// a launch costs 4-5 us here, more than the planning of so few documents.
 __global__ void __launch_bounds__(1024) k_bplan_one(BatchArgs a) {
-  __shared__ uint64_t red[5][kRedWaves];
-  uint64_t tot[5];
-  const uint64_t pre[5] = {0, 0, 0, 0, 0};
+  __shared__ uint64_t red[7][kRedWaves];
+  uint64_t tot[7];
+  const uint64_t pre[7] = {};
   plan_sums(a, 0, a.ndocs, tot, red);
   plan_number(a, 0, a.ndocs, pre, tot, red);
   __syncthreads();
@@ -2863,7 +2873,7 @@ template <int LINE>
 __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
   const BatchLds l = batch_stage(a);
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t nlanes = a.meta[kNLanes], nspec = a.meta[kNSpec];
+  const uint32_t nlanes = a.meta[kNLanes], nspec = a.meta[kNSpec], fine = a.meta[kFine];
   const uint32_t nst = (nspec + 63) / 64;  // speculative tiles first
   const bool ck_on = !a.meta[kNoWin];
   const uint32_t rm = refused_mask(a);
@@ -2898,7 +2908,7 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
     const uint8_t *lut = l.luts + 256 * (valid ? doc.inst : 0);
     const bool mine = valid && !spec_split(a, rm, doc);
     if (mine) {
-      if (jj) start = search_cert(src, doc.length, in.ca, lut, jj * a.fine_bytes, a.fine_bytes, kNone);
+      if (jj) start = search_cert(src, doc.length, in.ca, lut, jj * fine, fine, kNone);
       else if (doc.length) start = 0;
     }
     // a slice ends where the document's next non-empty lane's starts: in this tile, or past it
@@ -2909,7 +2919,7 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
     const uint32_t fs = (uint32_t)__shfl((int)start, f), fd = (uint32_t)__shfl((int)d, f);
     uint32_t s = 0, e = 0;
     if (start == kNone) {
-      s = e = min(jj * a.fine_bytes, doc.length);
+      s = e = min(jj * fine, doc.length);
     } else {
       s = start;
       if (after && fd == d) {
@@ -2917,7 +2927,7 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
       } else if (jj + (64 - lane) >= nl) {
         e = doc.length;
       } else {
-        const uint32_t x1 = (jj + (64 - lane)) * a.fine_bytes;
+        const uint32_t x1 = (jj + (64 - lane)) * fine;
         e = search_cert(src, doc.length, in.ca, lut, x1, doc.length - x1, doc.length);
       }
     }
@@ -2937,7 +2947,7 @@ __global__ void __launch_bounds__(1024) k_bcount(BatchArgs a) {
       ck.nlanes = a.max_lanes;
       ck.kslots = a.kslots;
       ck.j = j;
-      ck.jl = jj * a.fine_bytes;
+      ck.jl = jj * fine;
       ck.mis0 = (uint32_t)(ck.base & (kWin - 1));
     }
     const bool halted = walk_wave<LINE, true, true>(L, tb, src, doc.length, s, e, doc.length, start != kNone, ck);
@@ -3072,7 +3082,7 @@ __global__ void __launch_bounds__(256) k_bsplit(BatchArgs a) {
 __device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t lane = threadIdx.x & 63;
   const bool win = !a.meta[kNoWin];
-  const uint32_t rm = refused_mask(a);
+  const uint32_t rm = refused_mask(a), fine = a.meta[kFine];
   bool any_lane = false;
   // the next document's lane range and the next chunk's lanes load while the current ones
   // are scanned (a document of thousands of lanes would otherwise wait on every chunk)
@@ -3090,7 +3100,7 @@ __device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint
     const DocDev doc = a.docs[d];
     // walked lanes per plan lane (a power of two up to 64, so that 64-lane chunks hold whole ones)
     const bool split = spec_split(a, rm, doc);
-    const uint32_t ratio = split ? 1 : a.lane_bytes / a.fine_bytes;
+    const uint32_t ratio = split ? 1 : a.lane_bytes / fine;
     const uint64_t heads = ratio < 64 ? ~0ull / ((1ull << ratio) - 1) : 1;  // the first bit of every `ratio`
     uint32_t run = 0, nsl = 0, halt = kNone, err = doc.length;
     bool nowin = !win;
@@ -3143,7 +3153,7 @@ __device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint
         // the halted slice may run past this chunk's lanes (empty ones, from there to its end):
         // the windows in it find it through them
         const uint32_t end = (uint32_t)__shfl((int)en0, f);  // > 0: a halted slice is not empty
-        const uint32_t far = min(nl - 1, (end - 1) / (split ? a.spec_bytes : a.fine_bytes));
+        const uint32_t far = min(nl - 1, (end - 1) / (split ? a.spec_bytes : fine));
         for (uint32_t k = c + 64 + lane; win && k <= far; k += 64) a.lnz[lb + k] = halt;
         break;
       }
@@ -3395,7 +3405,7 @@ __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
     __syncthreads();
   }
   uint32_t *stage = reinterpret_cast<uint32_t *>(l.ring) + wid * kStageWords;
-  const uint32_t ntiles = a.meta[kNTiles];
+  const uint32_t ntiles = a.meta[kNTiles], fine = a.meta[kFine];
   const uint32_t rm = refused_mask(a);
   const uint32_t per_g = (ntiles + gridDim.x - 1) / gridDim.x;
   const uint32_t g_lo = min(ntiles, blockIdx.x * per_g), g_hi = min(ntiles, g_lo + per_g), span = g_hi - g_lo;
@@ -3431,7 +3441,7 @@ __global__ void __launch_bounds__(1024) k_bemit_win(BatchArgs a) {
     c.lb = a.lane_base[d];
     c.nl = a.lanes_of[d];
     const bool split = spec_split(a, rm, doc);
-    c.lnom = split ? a.spec_bytes : a.fine_bytes;
+    c.lnom = split ? a.spec_bytes : fine;
     c.sb = split ? a.spec_base[d] : kNone;
     c.out0 = (uint32_t)a.res[d].tok_offset;
     c.lim = c.out0 + (uint32_t)a.res[d].ntokens;  // the document's outputs end here
@@ -4134,6 +4144,7 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   a.lane_bytes = lane_bytes;
   a.fine_bytes = batch_fine_bytes(nbytes, lane_bytes, chosen);
   a.max_lanes = batch_max_lanes(ndocs, nbytes, a.fine_bytes);
+  a.plan_lanes = batch_max_lanes(ndocs, nbytes, lane_bytes);
   // workspace: the per-lane arrays are sized for the most lanes the byte count allows
   uint8_t *w = static_cast<uint8_t *>(ws);
   a.meta = reinterpret_cast<uint32_t *>(w);

@@ -85,3 +85,19 @@ def test_more_tiles_than_the_bytes_hold(setup, stray, offsets):
     check(setup, data, [(i, n - i, 2, 0) for i in range(6)], lane=65536, offsets=offsets)
     check(setup, data, [(0, n, 2, 0)] + [(0, n, 2, 1)] * 7, offsets=offsets)
     check(setup, plain, [(0, n, 0, 0), (3, n - 3, 1, 0), (0, n, 1, 0)], lane=16384, offsets=offsets)
+
+
+@pytest.mark.parametrize("ndocs", [40, 300])
+def test_short_documents_over_the_same_bytes(setup, ndocs):
+    """More finely walked lanes than the workspace's: the batch is walked in its plan's lanes, one to a
+    document here.  More of the plan's lanes than the bytes hold stops it."""
+    data = workloads.clike(1000, 9).copy()
+    data[700] = 1
+    check(setup, data, [(0, 1000, d % 2, 0) for d in range(ndocs)], offsets=True)
+    check(setup, data, [(d % 7, 1000 - d % 11 - 7, d % 3, d % 2) for d in range(ndocs)])
+    n = 60_000
+    big = torch.from_numpy(workloads.clike(n, 4)).cuda()
+    for lane in (0, 1024):
+        r = setup[2].run(big, np.array([(0, n, 0, 0)] * 3, dtype=P.DOC_DTYPE), cap=3 * n,
+                         opts=P.RunOpts(lane_bytes=lane) if lane else None)
+        assert r.status == P.LEX_EINVAL and (r.docs["status"] == P.LEX_EINVAL).all()
