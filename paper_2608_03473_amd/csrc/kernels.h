@@ -142,8 +142,10 @@ struct BatchTables {
   uint32_t ninst;
   BatchInstHost inst[kBatchMaxInst];
 };
-// Workspace of a batch of ndocs documents over nbytes bytes with lane target lane_bytes (chosen:
-// by the caller; a default lane may be walked in finer ones, its slices counted as planned).
+// Workspace that a batch of ndocs documents over nbytes bytes needs with lane target lane_bytes (chosen:
+// by the caller; a default lane may be walked in finer ones, its slices counted as planned), and
+// one that also serves every smaller batch.
+size_t batch_need_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen);
 size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen);
 // LDS of the batched lane-emit workgroup (the count walk needs less): 0 if it does not fit.
 // (The windowed emit takes as many waves as fit beside the table, or stands down.)

@@ -4077,9 +4077,10 @@ static uint32_t batch_spec_bytes(uint32_t) { return kSpecX; }
 // 64k lanes and at least kFineLane bytes.  Below about that many lanes the count pass takes as long
 // as its longest walk (73 cycles a byte), above it the lanes fill the chip and shorter ones
 // only add their unaligned ends.
+constexpr uint64_t kFineLanes = 64u << 10;
 static uint32_t batch_fine_bytes(uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
   uint32_t f = lane_bytes;
-  while (!chosen && f % 32 == 0 && f / 2 >= kFineLane && lane_bytes / f < 64 && nbytes / (f / 2) <= (64u << 10)) f /= 2;
+  while (!chosen && f % 32 == 0 && f / 2 >= kFineLane && lane_bytes / f < 64 && nbytes / (f / 2) <= kFineLanes) f /= 2;
   return f;
 }
 
@@ -4099,8 +4100,7 @@ static uint32_t batch_max_tiles(uint32_t ndocs, uint64_t nbytes) {
   return (uint32_t)std::min<uint64_t>(0xFFFFFFF0ull, 2ull * ndocs + nbytes / (64 * kWin) + 1);
 }
 
-size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
-  const uint32_t fine = batch_fine_bytes(nbytes, lane_bytes, chosen);
+static size_t batch_layout(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, uint32_t fine) {
   const uint64_t nl = batch_max_lanes(ndocs, nbytes, fine);
   const uint64_t ns = batch_max_spec(ndocs, nbytes, lane_bytes);
   const uint64_t nt = batch_max_tiles(ndocs, nbytes);
@@ -4111,6 +4111,20 @@ size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_byte
          align256((size_t)nt * 4);
 }
 
+size_t batch_need_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
+  return batch_layout(ndocs, nbytes, lane_bytes, batch_fine_bytes(nbytes, lane_bytes, chosen));
+}
+
+// The need falls where a longer lane is walked from some size on, so a default lane's workspace is
+// sized for the largest need of any size up to this one (16 documents: 8.36 MB at 8 MiB, 6.40 MB
+// needed at 8 MiB + 128 B).
+size_t batch_workspace_bytes(uint32_t ndocs, uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
+  size_t need = batch_need_bytes(ndocs, nbytes, lane_bytes, chosen);
+  for (uint32_t f = lane_bytes / 2; !chosen && f >= kFineLane; f /= 2)
+    need = std::max(need, batch_layout(ndocs, std::min(nbytes, kFineLanes * f + f - 1), lane_bytes, f));
+  return need;
+}
+
 size_t batch_emit_lds_bytes(int nrows, uint32_t ninst) {
   const size_t b = batch_lds_offset(nrows, ninst) + 256 * (size_t)kRingBytes;
   return b <= 160 * 1024 ? b : 0;
@@ -4119,7 +4133,7 @@ size_t batch_emit_lds_bytes(int nrows, uint32_t ninst) {
 hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbytes, const void *docs, uint32_t ndocs,
                      uint32_t lane_bytes, bool chosen, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap,
                      void *res, ResultDev *total, void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t const *ev) {
-  if (ws_bytes < batch_workspace_bytes(ndocs, nbytes, lane_bytes, chosen)) return hipErrorInvalidValue;
+  if (ws_bytes < batch_need_bytes(ndocs, nbytes, lane_bytes, chosen)) return hipErrorInvalidValue;
   if (!batch_emit_lds_bytes(bt.nrows, bt.ninst) || bt.ninst == 0 || bt.ninst > (uint32_t)kMaxInst) return hipErrorInvalidValue;
   BatchArgs a{};
   a.table = bt.table;

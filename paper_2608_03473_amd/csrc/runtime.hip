@@ -607,7 +607,7 @@ int lex_run_batch(const lex_batch *b, const uint8_t *d_bytes, uint64_t nbytes, c
   int rc = batch_lane_bytes(opts, nbytes, lb);
   if (rc != LEX_OK) return rc;
   const bool chosen = opts && opts->lane_bytes;
-  if (ws_bytes < lexk::batch_workspace_bytes(ndocs, nbytes, lb, chosen)) return LEX_ELIMIT;
+  if (ws_bytes < lexk::batch_need_bytes(ndocs, nbytes, lb, chosen)) return LEX_ELIMIT;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != b->device) return LEX_EDEVICE;
   hipEvent_t const *ev = opts && opts->events ? reinterpret_cast<hipEvent_t const *>(opts->events) : nullptr;
