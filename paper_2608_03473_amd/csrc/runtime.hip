@@ -152,6 +152,7 @@ int finish_compile(lex_dfa *d, lex_dfa **out, char *err, size_t errlen) {
 struct Resolved {
   uint32_t lane_bytes;
   uint32_t block;
+  uint32_t large_block;  // the block of a workspace that holds no smaller one's arrays (fit_block)
   int path;  // 1 pipeline, 2 fused (one pass or separate launches)
   bool serial;
   int table;  // 0 exact, 1 discard
@@ -207,6 +208,7 @@ int resolve(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *o, Resol
   // A short scan's lanes spread over more CUs in small workgroups (64 KiB of JSON counted in
   // 25 us in one of 1024 lanes: its 16 waves share one LDS).
   const uint64_t lb0 = o && o->lane_bytes ? o->lane_bytes : default_lane_bytes(n, false);
+  r.large_block = r.block;
   if (!r.onepass && !bt && !r.hybrid && n / lb0 < kSmallLanes) r.block = std::min<uint32_t>(r.block, 256);
   if (r.hybrid) {  // speculative lanes and cuts, then the pipeline's count, scan and emit
     r.onepass = false;
@@ -228,6 +230,17 @@ int resolve(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *o, Resol
   if (r.serial && n > 0xFFFFFFF0ull) return LEX_ELIMIT;
   r.lane_bytes = lb;
   return LEX_OK;
+}
+
+size_t need_bytes(uint64_t n, const Resolved &r) {
+  return lexk::workspace_bytes((uint32_t)n, r.lane_bytes, r.block, r.path == 1 && !r.hybrid, r.windowed, r.hybrid);
+}
+
+// A short scan's small workgroups need some KiB more for their arrays than the largest ones.  A
+// workspace that holds only those (the static scratch at its limit, one sized for a larger scan
+// with the same options) takes the largest.
+void fit_block(uint64_t n, size_t ws_bytes, Resolved &r) {
+  if (r.block < r.large_block && need_bytes(n, r) > ws_bytes) r.block = r.large_block;
 }
 
 // Definitions of the C-ABI into the compiler's form; exclude is the reserved byte or -1.
@@ -353,7 +366,7 @@ int lex_tables(const lex_dfa *d, int mode, uint32_t *table, size_t table_entries
 size_t lex_workspace_size(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *opts) {
   Resolved r;
   if (!d || n > 0xFFFFFFF0ull || resolve(d, n, mode, opts, r) != LEX_OK) return 0;
-  return lexk::workspace_bytes((uint32_t)n, r.lane_bytes, r.block, r.path == 1 && !r.hybrid, r.windowed, r.hybrid);
+  return need_bytes(n, r);
 }
 
 int lex_plan(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *opts, lex_plan_info *out) {
@@ -454,6 +467,7 @@ int lex_run(const lex_dfa *d, const uint8_t *d_bytes, uint64_t n, int mode, uint
   Resolved r;
   rc = resolve(d, n, mode, opts, r);
   if (rc != LEX_OK) return rc;
+  fit_block(n, ws_bytes, r);
   DevCopy *dc = device_copy(const_cast<lex_dfa *>(d));
   if (!dc) return LEX_EDEVICE;
   return enqueue_scan(d, dc, r, d_bytes, n, d_kinds, d_lens, d_offsets, cap, d_result, d_ws, ws_bytes, opts, stream);
@@ -467,9 +481,8 @@ int lex_run_static(const lex_dfa *d, const uint8_t *d_bytes, uint64_t n, int mod
   Resolved r;
   rc = resolve(d, n, mode, opts, r);
   if (rc != LEX_OK) return rc;
-  const size_t need =
-      lexk::workspace_bytes((uint32_t)n, r.lane_bytes, r.block, r.path == 1 && !r.hybrid, r.windowed, r.hybrid);
-  if (need > (size_t)LEX_STATIC_WS_BYTES) return LEX_ELIMIT;
+  fit_block(n, LEX_STATIC_WS_BYTES, r);
+  if (need_bytes(n, r) > (size_t)LEX_STATIC_WS_BYTES) return LEX_ELIMIT;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return LEX_EDEVICE;
   DevCopy *dc = find_copy(d, dev);  // never uploads: that would allocate

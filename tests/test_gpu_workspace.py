@@ -46,3 +46,35 @@ def test_batch_workspace_grows_with_the_bytes():
     assert k == want.ntokens
     assert torch.equal(kinds[:k], want.kinds) and torch.equal(lens[:k], want.lens)
     np.testing.assert_array_equal(res.cpu().numpy().view(P.DOC_RESULT_DTYPE), want.docs)
+
+
+def test_static_scratch_at_its_limit():
+    """The largest scan that the static scratch holds in the largest workgroups, though not in the
+    small ones that a scan of fewer than 64k lanes takes by default."""
+    lx, mode, lane = compiled("json"), P.LEX_MODE_DISCARD, 4096
+    opts, large = P.RunOpts(lane_bytes=lane), P.RunOpts(lane_bytes=lane, block_threads=1024)
+    lo, hi = 1, 64 << 10  # lanes
+    while lo + 1 < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if lx.workspace_size(mid * lane, mode, large) <= 64 << 20 else (lo, mid)
+    n = lo * lane
+    assert lx.plan(n, mode, opts)["block_threads"] == 256 and lx.workspace_size(n, mode, opts) > 64 << 20
+    data = torch.full((n,), 0x20, dtype=torch.uint8, device="cuda")
+    part = torch.from_numpy(workloads.json(1 << 20, 1)).cuda()
+    for a in range(0, n - part.numel(), 5 << 20):
+        data[a: a + part.numel()] = part
+    print(f"[case] static scan of {n} bytes", flush=True)
+    want = lx.run(data, mode=mode, opts=large)
+    kinds, lens = torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+    res = torch.zeros(3, dtype=torch.int64, device="cuda")
+    ws = torch.empty(lx.workspace_size(n, mode, large), dtype=torch.uint8, device="cuda")
+    for static in (True, False):
+        kinds.zero_(), lens.zero_(), res.zero_()
+        if static:
+            lx.run_static_into(data, n, mode, kinds, lens, None, n, res, opts)
+        else:
+            lx.run_into(data, n, mode, kinds, lens, None, n, res, ws, opts)
+        r = res.cpu().numpy()
+        assert (int(r[0]), int(r[1]), int(np.int32(r[2] & 0xFFFFFFFF))) == (want.ntokens, want.error_offset, want.status)
+        assert int(r[2]) >> 32 == want.nslices and want.ntokens > 1000
+        assert torch.equal(kinds[: want.ntokens], want.kinds) and torch.equal(lens[: want.ntokens], want.lens)
