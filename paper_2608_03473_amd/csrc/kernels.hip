@@ -2297,7 +2297,8 @@ struct BatchArgs {
   // lane_bytes: the plan's lane, which slices are counted by; fine_bytes: the lane to walk
   // (lane_bytes over a power of two: a small batch has too few lanes of its own to fill the chip).
   // Documents that share bytes may have more walked lanes than the workspace's max_lanes; they are
-  // then walked in the plan's (meta[kFine]), of which plan_lanes are accepted.
+  // then walked in the plan's (meta[kFine]), of which plan_lanes are accepted, and so are batches
+  // with split documents (plan_number).
   uint32_t ndocs, lane_bytes, fine_bytes, max_lanes, plan_lanes;
   uint32_t *meta;  // kBatchMeta words: queues, lane count
   uint64_t *part;  // kDocGroups x kPartWords: per-group sums of the planning and result kernels
@@ -2535,7 +2536,10 @@ __device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uin
                                             const uint64_t (&tot)[7], uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  const bool fits_fine = tot[0] + tot[1] <= a.max_lanes;
+  // Beside split documents the count pass takes as long as their speculative walks, and finer lanes
+  // only lengthen the document pass: 64 documents, one of 1.4 MB, 30 KB refused, 560 us in 128-byte
+  // lanes, 436 in the plan's.
+  const bool fits_fine = tot[0] + tot[1] <= a.max_lanes && tot[2] == 0;
   const uint32_t fine = fits_fine ? a.fine_bytes : a.lane_bytes;
   // 64-bit: a hostile table may ask for 2^32 lanes
   uint64_t r[4] = {fits_fine ? pre[0] : pre[5], fits_fine ? tot[0] + pre[1] : tot[5] + pre[6], pre[2], pre[3]};
@@ -2576,6 +2580,18 @@ __device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uin
   }
 }
 
+// p[0, n) = d, by a wave, four values to a store.
+__device__ __forceinline__ void fill_run(uint32_t *p, uint32_t n, uint32_t d) {
+  const uint32_t v[4] = {d, d, d, d};
+  for (uint32_t k = (threadIdx.x & 63) * 4; k < n; k += 256) {
+    if (k + 4 <= n) {
+      __builtin_memcpy(p + k, v, sizeof v);
+    } else {
+      for (uint32_t q = k; q < n; ++q) p[q] = d;
+    }
+  }
+}
+
 // A wave per document: the lane -> document map.
 __device__ __forceinline__ void map_docs(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t lane = threadIdx.x & 63;
@@ -2585,12 +2601,12 @@ __device__ __forceinline__ void map_docs(const BatchArgs &a, uint32_t wave, uint
   for (uint32_t d = wave; d < a.ndocs; d += nwaves) {
     const uint32_t lb = a.lane_base[d], nl = a.lanes_of[d];
     const DocDev doc = a.docs[d];
-    for (uint32_t k = lane; k < nl; k += 64) a.lane_doc[lb + k] = d;
+    fill_run(a.lane_doc + lb, nl, d);
     if (spec_split(a, refused_mask(a), doc))
       for (uint32_t k = lane; k < nl; k += 64) a.spec_doc[a.spec_base[d] + k] = d;
     if (win) {
       const uint32_t tb = a.tile_base[d], nt = doc_tiles(base + doc.offset, doc.length);
-      for (uint32_t k = lane; k < nt; k += 64) a.tile_doc[tb + k] = d;
+      fill_run(a.tile_doc + tb, nt, d);
     }
   }
 }
@@ -3078,17 +3094,144 @@ __global__ void __launch_bounds__(256) k_bsplit(BatchArgs a) {
   }
 }
 
-// A wave per document: its first halted lane and the start of its failed token, the token
+// A thread's K consecutive values.
+template <int K>
+__device__ __forceinline__ void load_run(const uint32_t *p, uint32_t (&v)[K]) {
+  __builtin_memcpy(v, p, sizeof v);
+}
+
+// A document's pass, by a wave: its first halted lane and the start of its failed token, the token
 // count up to and including it, in-document prefixes of the lane counts, non-empty slices.
 // Slices are the plan's: where the walked lanes are finer, a plan lane has one when any of its
-// walked lanes has.  True if some document of this wave's takes the lane emit.
-__device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
+// walked lanes has (fold: threads per plan lane, a power of two up to 8).  True if the document
+// takes the lane emit.
+//
+// K: lanes to a thread.  A long document is a chain of steps, of 64 lanes at a lane to a thread (65
+// documents, one of 2.4 MB in 128-byte lanes: 187 us, their walks 34); with as many lanes to a
+// thread as a plan lane has the chain is as long as its plan's lanes make it, but a step takes
+// about four times as long.
+template <int K>
+__device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t d, uint32_t lb, uint32_t nl, const DocDev &doc,
+                                         uint32_t lane_bytes, uint32_t fold) {
   const uint32_t lane = threadIdx.x & 63;
   const bool win = !a.meta[kNoWin];
+  // the first bit of every `fold`
+  const uint64_t heads = fold == 1   ? ~0ull
+                         : fold == 2 ? 0x5555555555555555ull
+                         : fold == 4 ? 0x1111111111111111ull
+                                     : 0x0101010101010101ull;
+  uint32_t run = 0, nsl = 0, halt = kNone, err = doc.length;
+  bool nowin = !win;
+  int32_t zrun = -1;  // last non-empty lane of the earlier chunks
+  // the next chunk's lanes load while the current ones are scanned (a document of thousands of
+  // lanes would otherwise wait on every chunk); lanes past the document's last reload that lane
+  // (any defined value does)
+  struct Run {
+    uint32_t cn[K], hf[K], cu[K], en[K];
+  };
+  auto load = [&](uint32_t c, Run &r) {
+    const uint32_t i0 = c + lane * K;
+    if (K > 1 && i0 + K <= nl) {
+      load_run<K>(a.counts + lb + i0, r.cn);
+      load_run<K>(a.halted + lb + i0, r.hf);
+      load_run<K>(a.cuts + lb + i0, r.cu);
+      load_run<K>(a.ends + lb + i0, r.en);
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const uint32_t jc = lb + min(i0 + q, nl - 1);
+      r.cn[q] = a.counts[jc];
+      r.hf[q] = a.halted[jc];
+      r.cu[q] = a.cuts[jc];
+      r.en[q] = a.ends[jc];
+    }
+  };
+  Run next;
+  load(0, next);
+  for (uint32_t c = 0; c < nl; c += 64 * K) {
+    const Run x = next;
+    if (c + 64 * K < nl) load(c + 64 * K, next);  // wave-uniform
+    const uint32_t i0 = c + lane * K, j0 = lb + i0;
+    uint32_t cnt[K], sum = 0, upto = 0, end = 0;  // upto: the thread's tokens up to its first halted lane
+    bool ne[K], bad = false;
+    int hq = K;  // its place
+    int32_t z = -1;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const bool ok = i0 + q < nl;
+      cnt[q] = ok ? x.cn[q] : 0;
+      ne[q] = ok && x.cu[q] < x.en[q];
+      sum += cnt[q];
+      z = ne[q] ? (int32_t)(j0 + q) : z;
+      bad = bad || (ok && (x.hf[q] & 2));
+      if (hq == K) {
+        upto = sum;
+        if (ok && (x.hf[q] & 1)) hq = q, end = x.en[q];
+      }
+    }
+    uint32_t incl = sum;
+    for (int k = 1; k < 64; k <<= 1) {
+      const uint32_t v = (uint32_t)__shfl_up((int)incl, k);
+      const int32_t zz = __shfl_up(z, k);
+      if ((int)lane >= k) {
+        incl += v;
+        z = max(z, zz);
+      }
+    }
+    int32_t zp = __shfl_up(z, 1);  // the last non-empty lane before the thread's
+    zp = max(lane ? zp : -1, zrun);
+    const unsigned long long hb = __ballot(hq < K);
+    const int f = hb ? __ffsll(hb) - 1 : 63;
+    const int fq = K > 1 ? __shfl(hq, f) : 0;
+    if (hb) err = a.lane_pre[lb + c + (uint32_t)(f * K + fq)];  // wave-uniform
+    uint32_t pre = run + incl - sum;
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      any = any || (ne[q] && (!hb || (int)lane < f || ((int)lane == f && q <= fq)));
+      zp = ne[q] ? (int32_t)(j0 + q) : zp;
+      if (i0 + q < nl) {
+        a.lane_pre[j0 + q] = pre;
+        if (win) a.lnz[j0 + q] = (uint32_t)zp;
+      }
+      pre += cnt[q];
+    }
+    unsigned long long live = __ballot(any);
+    for (uint32_t r = 1; r < fold; r <<= 1) live |= live >> r;
+    nsl += __popcll(live & heads);
+    nowin = nowin || __any(bad);
+    zrun = max(zrun, (int32_t)__shfl(z, 63));
+    run += (uint32_t)__shfl((int)(incl - sum + upto), f);
+    if (hb) {  // wave-uniform
+      halt = lb + c + (uint32_t)(f * K + fq);
+      // the halted slice may run past this chunk's lanes (empty ones, from there to its end):
+      // the windows in it find it through them
+      const uint32_t e = (uint32_t)__shfl((int)end, f);  // > 0: a halted slice is not empty
+      const uint32_t far = min(nl - 1, (e - 1) / lane_bytes);
+      for (uint32_t k = c + 64 * K + lane; win && k <= far; k += 64) a.lnz[lb + k] = halt;
+      break;
+    }
+  }
+  if (lane == 0) {
+    a.doc_ntok[d] = run;
+    a.doc_halt[d] = halt;
+    a.doc_err[d] = err;
+    a.doc_nsl[d] = nsl;
+    a.doc_win[d] = !nowin;  // a fallback or a long slice: the lane emit writes it
+  }
+  return nowin;
+}
+
+// A wave per document.  True if some document of this wave's takes the lane emit.  FINE: lanes finer
+// than the plan's may be walked (without them fewer registers, more documents at a time).
+constexpr uint32_t kLongDoc = 512;  // walked lanes from which a thread takes a plan lane's (eight steps against one)
+template <bool FINE>
+__device__ __forceinline__ bool doc_passes(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t rm = refused_mask(a), fine = a.meta[kFine];
+  const uint32_t ratio = FINE ? a.lane_bytes / fine : 1;  // 1, 2, 4 or 8; 1 beside split documents
   bool any_lane = false;
-  // the next document's lane range and the next chunk's lanes load while the current ones
-  // are scanned (a document of thousands of lanes would otherwise wait on every chunk)
+  // the next document's lane range loads while the current one is scanned
   uint32_t n_lb = 0, n_nl = 1;
   if (wave < a.ndocs) {
     n_lb = a.lane_base[wave];
@@ -3101,74 +3244,12 @@ __device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t wave, uint
       n_nl = a.lanes_of[d + nwaves];
     }
     const DocDev doc = a.docs[d];
-    // walked lanes per plan lane (a power of two up to 64, so that 64-lane chunks hold whole ones)
-    const bool split = spec_split(a, rm, doc);
-    const uint32_t ratio = split ? 1 : a.lane_bytes / fine;
-    const uint64_t heads = ratio < 64 ? ~0ull / ((1ull << ratio) - 1) : 1;  // the first bit of every `ratio`
-    uint32_t run = 0, nsl = 0, halt = kNone, err = doc.length;
-    bool nowin = !win;
-    int32_t zrun = -1;  // last non-empty lane of the earlier chunks
-    // lanes past the document's last reload that lane (any defined value does)
-    auto load = [&](uint32_t c, uint32_t &cn, uint32_t &hf, uint32_t &cu, uint32_t &en) {
-      const uint32_t jc = lb + min(c + lane, nl - 1);
-      cn = a.counts[jc];
-      hf = a.halted[jc];
-      cu = a.cuts[jc];
-      en = a.ends[jc];
-    };
-    uint32_t q_cn, q_hf, q_cu, q_en;
-    load(0, q_cn, q_hf, q_cu, q_en);
-    for (uint32_t c = 0; c < nl; c += 64) {
-      const uint32_t cn0 = q_cn, hf0 = q_hf, cu0 = q_cu, en0 = q_en;
-      if (c + 64 < nl) load(c + 64, q_cn, q_hf, q_cu, q_en);  // wave-uniform
-      const bool ok = c + lane < nl;
-      const uint32_t j = lb + c + lane;
-      const uint32_t cnt = ok ? cn0 : 0;
-      const uint32_t hf = ok ? hf0 : 0;
-      const bool h = hf & 1;
-      const bool ne = ok && cu0 < en0;
-      uint32_t incl = cnt;
-      int32_t z = ne ? (int32_t)j : zrun;
-      for (int k = 1; k < 64; k <<= 1) {
-        const uint32_t v = (uint32_t)__shfl_up((int)incl, k);
-        const int32_t zz = __shfl_up(z, k);
-        if ((int)lane >= k) {
-          incl += v;
-          z = max(z, zz);
-        }
-      }
-      const unsigned long long hb = __ballot(h), nb = __ballot(ne);
-      if (hb) err = a.lane_pre[lb + c + __ffsll(hb) - 1];  // wave-uniform
-      if (ok) {
-        a.lane_pre[j] = run + incl - cnt;
-        if (win) a.lnz[j] = (uint32_t)z;
-      }
-      nowin = nowin || __any(hf & 2);
-      zrun = __shfl(z, 63);
-      unsigned long long live = nb;
-      const int f = hb ? __ffsll(hb) - 1 : 63;
-      live &= (2ull << f) - 1;
-      for (uint32_t r = 1; r < ratio; r <<= 1) live |= live >> r;
-      nsl += __popcll(live & heads);
-      run += (uint32_t)__shfl((int)incl, f);
-      if (hb) {  // wave-uniform
-        halt = lb + c + f;
-        // the halted slice may run past this chunk's lanes (empty ones, from there to its end):
-        // the windows in it find it through them
-        const uint32_t end = (uint32_t)__shfl((int)en0, f);  // > 0: a halted slice is not empty
-        const uint32_t far = min(nl - 1, (end - 1) / (split ? a.spec_bytes : fine));
-        for (uint32_t k = c + 64 + lane; win && k <= far; k += 64) a.lnz[lb + k] = halt;
-        break;
-      }
-    }
-    if (lane == 0) {
-      a.doc_ntok[d] = run;
-      a.doc_halt[d] = halt;
-      a.doc_err[d] = err;
-      a.doc_nsl[d] = nsl;
-      a.doc_win[d] = !nowin;  // a fallback or a long slice: the lane emit writes it
-      any_lane |= nowin;
-    }
+    const uint32_t lane_bytes = spec_split(a, rm, doc) ? a.spec_bytes : fine;
+    const uint32_t k = !FINE || nl < kLongDoc ? 1 : ratio;  // wave-uniform
+    any_lane |= k == 8   ? doc_pass<8>(a, d, lb, nl, doc, lane_bytes, 1)
+                : k == 4 ? doc_pass<4>(a, d, lb, nl, doc, lane_bytes, 1)
+                : k == 2 ? doc_pass<2>(a, d, lb, nl, doc, lane_bytes, 1)
+                         : doc_pass<1>(a, d, lb, nl, doc, lane_bytes, ratio);
   }
   return any_lane;
 }
@@ -3227,9 +3308,10 @@ __device__ __forceinline__ void result_bad(const BatchArgs &a) {
   }
 }
 
+template <bool FINE>
 __global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
   if (a.meta[kBad]) return;
-  const bool any = doc_pass(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+  const bool any = doc_passes<FINE>(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
   if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;  // every writer stores the same value
 }
 
@@ -3259,7 +3341,7 @@ __global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
 __global__ void __launch_bounds__(1024) k_bdoc_one(BatchArgs a) {
   __shared__ uint64_t red[3][kRedWaves];
   if (a.meta[kBad]) return result_bad(a);
-  const bool any = doc_pass(a, threadIdx.x >> 6, blockDim.x >> 6);
+  const bool any = doc_passes<true>(a, threadIdx.x >> 6, blockDim.x >> 6);
   if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;
   __syncthreads();
   uint64_t tot[3];
@@ -3978,7 +4060,7 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
 // walk: 256 MiB of JSON in 512-byte lanes 291 us against 286.
 constexpr uint32_t kShortLane = 512, kShortLaneOne = 1024;
 // Batches: the shortest walked lane; what one workgroup plans and reports.
-constexpr uint32_t kFineLane = 128, kOneDocs = 64;
+constexpr uint32_t kFineLane = 128, kOneDocs = 64, kMaxRatio = 8;
 constexpr uint64_t kOneBytes = 4u << 20;
 
 static inline void mark(hipEvent_t const *ev, int i, hipStream_t s) {
@@ -4076,14 +4158,14 @@ hipError_t run_pipeline(const DevTable &t, const CertMap &cm, const uint8_t *in,
 // only), so their length, not their number, sets the walk kernel's time.
 static uint32_t batch_spec_bytes(uint32_t) { return kSpecX; }
 
-// The lane that is walked: the plan's, over a power of two up to 64, while that gives at most
+// The lane that is walked: the plan's, over a power of two up to kMaxRatio, while that gives at most
 // 64k lanes and at least kFineLane bytes.  Below about that many lanes the count pass takes as long
 // as its longest walk (73 cycles a byte), above it the lanes fill the chip and shorter ones
 // only add their unaligned ends.
 constexpr uint64_t kFineLanes = 64u << 10;
 static uint32_t batch_fine_bytes(uint64_t nbytes, uint32_t lane_bytes, bool chosen) {
   uint32_t f = lane_bytes;
-  while (!chosen && f % 32 == 0 && f / 2 >= kFineLane && lane_bytes / f < 64 && nbytes / (f / 2) <= kFineLanes) f /= 2;
+  while (!chosen && f % 32 == 0 && f / 2 >= kFineLane && lane_bytes / f < kMaxRatio && nbytes / (f / 2) <= kFineLanes) f /= 2;
   return f;
 }
 
@@ -4270,7 +4352,8 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
     k_bdoc_one<<<1, 1024, 0, s>>>(a);
     if (!launched()) return e;
   } else {
-    k_bdoc<<<gdoc, 256, 0, s>>>(a);
+    if (a.fine_bytes < a.lane_bytes) k_bdoc<true><<<gdoc, 256, 0, s>>>(a);
+    else k_bdoc<false><<<gdoc, 256, 0, s>>>(a);
     if (!launched()) return e;
     k_bscan_a<<<ngroups, 256, 0, s>>>(a);
     if (!launched()) return e;
