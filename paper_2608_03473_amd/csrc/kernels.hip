@@ -4058,7 +4058,10 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
 // Lanes below this walk in 64-byte stretches (walk_wave).  One pass: 100 MB in 512-byte lanes 198 us
 // against 210 in 128-byte stretches, 512 MiB in 2 KiB lanes 551 against 520.  The separate count
 // walk: 256 MiB of JSON in 512-byte lanes 291 us against 286.
-constexpr uint32_t kShortLane = 512, kShortLaneOne = 1024;
+// A separate count walk of few lanes, a workgroup of 256 to a CU at most, waits for its loads and not
+// for the LDS, and a 64-byte stretch loads while the one before is walked (2333 bytes of a
+// refused set, one lane: 105 us in 128-byte stretches, 99 so; path 1 on 3 KB 54 and 46).
+constexpr uint32_t kShortLane = 512, kShortLaneOne = 1024, kFewLanes = 64u << 10;
 // Batches: the shortest walked lane; what one workgroup plans and reports.
 constexpr uint32_t kFineLane = 128, kOneDocs = 64, kMaxRatio = 8;
 constexpr uint64_t kOneBytes = 4u << 20;
@@ -4085,7 +4088,7 @@ static hipError_t count_scan_emit(const DevTable &t, const WalkArgs &a0, const P
   const bool win = p.windowed;
   mark(ev, 1, s);
   if (!win) k_count<128, FUSED, false><<<p.nblocks, p.block, smem_c, s>>>(a);
-  else if (FUSED && p.lane_bytes < kShortLane) k_count<64, FUSED, true><<<p.nblocks, p.block, smem_c, s>>>(a);
+  else if (p.lane_bytes < kShortLane || p.nlanes < kFewLanes) k_count<64, FUSED, true><<<p.nblocks, p.block, smem_c, s>>>(a);
   else k_count<128, FUSED, true><<<p.nblocks, p.block, smem_c, s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -206,10 +206,11 @@ int resolve(const lex_dfa *d, uint64_t n, int mode, const lex_run_opts *o, Resol
   r.path = asked == 1 ? 1 : 2;
   r.block = r.onepass ? lexk::kChunkLanes : bt ? (uint32_t)bt : default_block(d->c.nrows);
   // A short scan's lanes spread over more CUs in small workgroups (64 KiB of JSON counted in
-  // 25 us in one of 1024 lanes: its 16 waves share one LDS).
+  // 25 us in one of 1024 lanes: its 16 waves share one LDS), the hybrid plan's cuts too (3 MB of a
+  // refused set that take its second route, in the lane emit: 1375 us, 1156 so).
   const uint64_t lb0 = o && o->lane_bytes ? o->lane_bytes : default_lane_bytes(n, false);
   r.large_block = r.block;
-  if (!r.onepass && !bt && !r.hybrid && n / lb0 < kSmallLanes) r.block = std::min<uint32_t>(r.block, 256);
+  if (!r.onepass && !bt && n / (r.hybrid ? spec : lb0) < kSmallLanes) r.block = std::min<uint32_t>(r.block, 256);
   if (r.hybrid) {  // speculative lanes and cuts, then the pipeline's count, scan and emit
     r.onepass = false;
     r.path = 1;
