@@ -980,6 +980,7 @@ struct WalkArgs {
   uint32_t block;         // lanes per count workgroup (lane_pre's groups)
   uint32_t block_shift;   // log2(block)
   int certified;          // slices end at certified bytes (not the hybrid plan's cuts)
+  uint32_t *alone;        // k_count in one workgroup: meta, written by it (else null, and k_scan follows)
   uint32_t *blk_tok;      // windowed: start of the failed token of a workgroup's first halted lane
   FastDiv lane_div;       // division by lane_bytes
   uint64_t *chunk_st;     // one pass: look-back status per workgroup of lanes
@@ -1259,6 +1260,23 @@ __global__ void __launch_bounds__(1024) k_count(WalkArgs a) {
     a.blk_big[blockIdx.x] = q.wsum[18];
     a.blk_lnz[blockIdx.x] = total ? (int32_t)(c0 + q.lane[total - 1]) : -1;
     if (a.blk_tok && f != kNone) a.blk_tok[blockIdx.x] = q.wsum[17];
+    if (a.alone) {  // what k_scan would write
+      a.blk_sum[0] = 0;
+      a.blk_lnz[0] = -1;
+      a.alone[0] = f;
+      a.alone[1] = q.wsum[18];
+      a.res->error_offset = f != kNone && a.blk_tok ? q.wsum[17] : a.n;
+      a.res->nslices = total;
+      if (f == kNone) {
+        a.res->ntokens = sum;
+        a.res->status = sum > a.cap ? -4 : 0;
+      }
+    }
+  }
+  if (a.alone && j < a.nlanes && j == q.wsum[16]) {  // the tokens up to the halted lane's halt
+    const uint32_t ntok = pre + incl;
+    a.res->ntokens = ntok;
+    a.res->status = ntok > a.cap ? -4 : 0;
   }
 }
 
@@ -4087,13 +4105,17 @@ static hipError_t count_scan_emit(const DevTable &t, const WalkArgs &a0, const P
   const size_t smem_e = lds_bytes(t.nrows, (int)p.block, true);
   const bool win = p.windowed;
   mark(ev, 1, s);
+  // one workgroup's count writes the result itself (2333 bytes of JSON: 35.4 us with k_scan's launch)
+  a.alone = p.nblocks == 1 && !a.hs.nblocks ? p.meta : nullptr;
   if (!win) k_count<128, FUSED, false><<<p.nblocks, p.block, smem_c, s>>>(a);
   else if (p.lane_bytes < kShortLane || p.nlanes < kFewLanes) k_count<64, FUSED, true><<<p.nblocks, p.block, smem_c, s>>>(a);
   else k_count<128, FUSED, true><<<p.nblocks, p.block, smem_c, s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   mark(ev, 2, s);
-  if (a.hs.nblocks)
+  if (a.alone)
+    ;
+  else if (a.hs.nblocks)
     k_hscan<<<1, 1024, 0, s>>>(a, p.meta);
   else
     k_scan<<<1, 1024, 0, s>>>(p.blk_sum, p.blk_fail, p.blk_nonempty, p.blk_big, p.blk_lnz, p.nblocks, p.block,
