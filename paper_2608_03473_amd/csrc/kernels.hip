@@ -1582,17 +1582,11 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb, 
     const uint32_t c = k * a.hs.S, end = (uint32_t)min<uint64_t>((uint64_t)c + kSpecX, a.n);
     const uint32_t bend = (uint32_t)min<uint64_t>((uint64_t)c + a.hs.S + kSpecX, a.n);  // the walk's end
     const uint32_t iw = (uint32_t)(((uint64_t)end - 1 + mis0) / kWin), w0 = iw * kWin - mis0;  // the last window
-    uint32_t st = tb.start, p = c, tok = c, lacc = c, at_end = 0;
-    uint64_t starts = 0;
-    bool known = false, same = false;
-    // a token start of the second walk: of the serial scan too, in the last window?
-    auto start = [&](uint32_t x) {
-      if (x < w0 || x >= end) return;
-      if (!known) starts = start_mask(a, tb, iw, mis0, end, at_end);
-      known = true;
-      same = same || ((starts >> (x - w0)) & 1);
-    };
+    uint32_t st = tb.start, p = c, tok = c, lacc = c;
+    uint64_t mine = 0;  // the second walk's token starts in the last window
+    auto start = [&](uint32_t x) { mine |= x >= w0 && x < end ? 1ull << (x - w0) : 0; };
     start(c);
+    bool same = false;
     int64_t nb = INT64_MIN;  // position of the block loaded ahead
     uint4 nv = make_uint4(0, 0, 0, 0);
     while (!same && tok < end && p < bend) {
@@ -1617,7 +1611,7 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb, 
       tok = me ? (uint32_t)blk + ((31 - __clz(me)) >> 1) : tok;
       lacc = ac ? (uint32_t)blk + (31 - __clz(ac)) - 15 : lacc;
       if (blk + 16 > (int64_t)w0)
-        for (uint32_t x = me; x && !same; x &= x - 1) start((uint32_t)blk + ((uint32_t)(__ffs(x) - 1) >> 1));
+        for (uint32_t x = me; x; x &= x - 1) start((uint32_t)blk + ((uint32_t)(__ffs(x) - 1) >> 1));
       p = (uint32_t)(blk + hi);
       if (st == tb.sink || st == tb.fail) {  // restart, as walk_spec does
         p = tok = st == tb.fail && tb.fail != tb.sink && lacc > tok ? lacc : tok + 1;
@@ -1630,8 +1624,9 @@ __device__ __forceinline__ void check_cuts(const WalkArgs &a, const Tables &tb, 
       }
     }
     const bool last = k + 1 == a.hs.ncoarse;
+    uint32_t at_end = 0;
+    if ((!same && mine) || (last && halts)) same = (start_mask(a, tb, iw, mis0, end, at_end) & mine) || same;
     if (last && halts) {  // a cut there, or a halt before the interval's end, and the plan falls back
-      if (!known) (void)start_mask(a, tb, iw, mis0, end, at_end);
       if (same || at_end == tb.sink || at_end == tb.fail) atomicMin(&a.res->nslices, 1u);
     } else if (!same) {
       atomicMin(&a.res->nslices, last ? a.hs.ncoarse - 1 : 1u);
