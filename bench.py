@@ -155,13 +155,14 @@ def main():
     ph_mean = phases.mean(axis=0)
     plan = lx.plan(n, mode, opts)
     if plan["path"] == 3:
-        # one pass: reset, the one-pass kernel (plan, count walk, look-back, windowed emit),
-        # scan, and the lane emit's fallback (it returns at once on a clean scan)
-        names = ["reset", "onepass", "scan", "fallback_emit"]
-        algo = {"reset": 0, "onepass": n + 5 * ntok, "scan": 0, "fallback_emit": 0}
+        # one pass: reset, then the one-pass kernel (plan, count walk, look-back, windowed emit and
+        # result); the last two phases of the library's events are empty
+        names = ["reset", "onepass"]
+        algo = {"reset": 0, "onepass": n + 5 * ntok}
     else:
         names = ["plan", "count_walk", "scan", "emit_walk"]
         algo = {"plan": n + n / 8, "count_walk": n, "scan": 0, "emit_walk": n + 5 * ntok}
+    ph_mean = ph_mean[: len(names)]
     dom = names[int(np.argmax(ph_mean))]
     achieved = algo[dom] / (ph_mean[names.index(dom)] * 1e-3) / 1e9
     gbs = n / (ms * 1e-3) / 1e9

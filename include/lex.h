@@ -151,8 +151,9 @@ int lex_tables(const lex_dfa *dfa, int mode, uint32_t *table, size_t table_entri
  * else as 2): 256-lane workgroups take their lanes in order, count-walk them, find their
  * first output slot by a look-back over the earlier workgroups' published totals, emit and
  * write the result, all in one launch; 0 = default: 3 where it applies, else 2.  block_threads:
- * threads per walk workgroup, 256, 512 or 1024 (0 = the largest whose LDS fits; one pass
- * uses 256 and a default path given another value takes path 2).  emit: 0 = default,
+ * threads per walk workgroup, 256, 512 or 1024 (0 = 256 for a scan of fewer than 65 536 lanes
+ * whose workspace holds it, else the largest whose LDS fits; one pass uses 256 and a default
+ * path given another value takes path 2).  emit: 0 = default,
  * 1 = lane emit only.  By default a scan of an automaton with at most 256 rows uses the
  * windowed emit: the count
  * walk records checkpoints every 64 bytes and the emit walk runs one thread per 64-byte
@@ -266,8 +267,12 @@ int lex_batch_create(const lex_dfa *const *dfas, const int32_t *modes, uint32_t 
 void lex_batch_free(lex_batch *batch);
 
 /* Workspace for ndocs documents over nbytes bytes (opts: lane_bytes; NULL = defaults).  A
- * batch's default lane is 1 KiB, doubled while nbytes / lane exceeds 2^20, up to 4 KiB;
- * pass the same opts (or the same nbytes with defaults) to lex_run_batch. */
+ * batch's default lane is 1 KiB, doubled while nbytes / lane exceeds 2^21, up to 4 KiB.  Slices
+ * are counted by it; below 32 MiB it is walked in finer lanes of 512, 256 or 128 bytes (not
+ * beside documents of a refused set that are split, nor where documents share so many bytes
+ * that the finer lanes outnumber the workspace's).  A lane that opts choose is walked as it is.
+ * A workspace of this size also serves every batch of fewer documents or bytes with the same
+ * opts (with the default lane, of the same default). */
 size_t lex_batch_workspace_size(const lex_batch *batch, uint32_t ndocs, uint64_t nbytes, const lex_run_opts *opts);
 
 /* Scans the ndocs documents of d_docs (device array) over d_bytes[0, nbytes) (device).

@@ -65,8 +65,8 @@ struct Plan {
   // Windowed scans in separate launches (in chunk_st's place): per workgroup of lanes, the
   // start of the failed token of its first halted lane.
   uint32_t *blk_tok;
-  int pipelined;           // slices are [cuts[j], cuts[j + 1]) (pipeline and hybrid plans)
-  // Hybrid plan (a refused set split speculatively; lane_bytes is the speculative lane):
+  int pipelined;           // slices are [cuts[j], cuts[j + 1]) (pipeline path)
+  // Hybrid plan's second route (a refused set split speculatively; lane_bytes is its lane):
   // per lane its cut, last restart and head/tail token starts, and the fall-back flag.
   int hybrid;
   uint32_t *spec_cut, *spec_rst, *spec_bits, *spec_fail;
@@ -114,12 +114,13 @@ hipError_t run_fused(const DevTable &t, const CertMap &cm, const uint8_t *cert_l
                      const Plan &p, bool serial, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap,
                      ResultDev *res, hipStream_t s, hipEvent_t const *ev);
 
-// Hybrid plan for a refused set: speculative walks and their cuts, then the pipeline's count
-// walk, scan and emit over those cuts.
+// Hybrid plan for a refused set: cuts by state, scan and windowed emit; where they do not stand (or
+// without the windowed emit) speculative walks and their cuts, then the pipeline's count walk, scan
+// and emit over those.
 hipError_t run_hybrid(const DevTable &t, const CertMap &cm, const uint8_t *in, const Plan &p, uint8_t *kinds,
                       uint32_t *lens, uint64_t *offs, uint64_t cap, ResultDev *res, hipStream_t s, hipEvent_t const *ev);
-// One pass (windowed scans, block == kChunkLanes): plan, count walk, look-back and windowed
-// emit in one launch, then the scan and the lane emit's fallback.
+// One pass (windowed scans, block == kChunkLanes): plan, count walk, look-back, windowed emit and the
+// result in one launch, after a reset of the look-back state where there are several groups.
 hipError_t run_onepass(const DevTable &t, const CertMap &cm, const uint8_t *cert_lut, const uint8_t *in,
                        const Plan &p, bool serial, uint8_t *kinds, uint32_t *lens, uint64_t *offs, uint64_t cap,
                        ResultDev *res, hipStream_t s, hipEvent_t const *ev);

@@ -586,8 +586,8 @@ __device__ __forceinline__ void ck_maybe(const CkSink &c, const LaneState &L, ui
 // offsets (see Ring), so the emit steps need no branch.
 template <bool EMIT, bool MONO, bool FAST>
 __device__ __forceinline__ void block16(LaneState &L, Ring &r, const Tables &tb, const uint4 &v, uint32_t blk) {
-  if (!EMIT && !MONO) {
-    // count walk of a non-monotone automaton: each step shifts its COUNT and EMIT bits into
+  if (!EMIT) {
+    // count walk of a slice that falls back (walk_wave): each step shifts its COUNT and EMIT bits into
     // m (step k's pair lands in bits 2k, 2k + 1) and its ACC bit into a (bit 16 + k); the
     // last accepting step's row is recomputed only if a fallback needs it (kLazyRow)
     uint32_t m = 0, ac = 0, e = L.st;
@@ -608,24 +608,6 @@ __device__ __forceinline__ void block16(LaneState &L, Ring &r, const Tables &tb,
       L.lblk = blk;
       L.lst0 = st0;
     }
-    return;
-  }
-  if (!EMIT && MONO) {
-    // count walk of a monotone automaton: the COUNT and EMIT bits of the 16 steps are
-    // shifted into m (step k's pair lands in bits 2k, 2k + 1) and the COUNT bits popcounted
-    // once.
-    uint32_t m = 0, e = L.st;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      e = entry_from(tb, e, byte_of(v, k));
-      m = __builtin_amdgcn_alignbit(e, m, 2);
-    }
-    L.st = e & kRowMask;
-    L.cnt += __builtin_popcount(m & 0x55555555u);
-    // start of the token in progress: the last step at which a token ended, kept or
-    // discarded (only read by checkpoints)
-    const uint32_t me = m & 0xAAAAAAAAu;
-    L.tok = me ? blk + ((31 - __clz(me)) >> 1) : L.tok;
     return;
   }
   if (EMIT && FAST) {
@@ -694,8 +676,8 @@ __device__ __forceinline__ bool walk(LaneState &L, Ring &r, const Tables &tb, co
   }
   if (b0 >= (int64_t)e) return finish<EMIT, MONO>(L, r, tb, in, e);
   uint32_t blk = (uint32_t)b0;  // > s and 16-aligned in memory from here on
-  // Lines of kBlocks blocks: whole 128-byte lines for the count walk and the packed
-  // emit walk, single blocks for the generic emit walk.
+  // Lines of kBlocks blocks: whole 128-byte lines for the count walk and a monotone automaton's
+  // packed emit walk, single blocks for the other emit walks.
   constexpr int kBlocks = EMIT ? (FAST && MONO ? 8 : 1) : 8;
   // full blocks up to a line boundary
   while (blk + 16 <= e && (reinterpret_cast<uintptr_t>(in + blk) & (16 * kBlocks - 1))) {
@@ -1427,8 +1409,8 @@ __global__ void __launch_bounds__(1024) k_emit(WalkArgs a) {
 }
 
 // ---------------------------------------------------------- (e) windowed emit
-// For a monotone automaton whose token ends are all counted, and a scan with no halted
-// slice, the emit needs no lane-long walks.  Every lane starts at a certified byte, where
+// For a monotone automaton whose token ends are all counted, the emit needs no lane-long
+// walks.  Every lane starts at a certified byte, where
 // the serial lexer also starts a token (Theorem 1), so the lanes' states, counts and token
 // starts agree with the serial lexer's everywhere; the count walk left them at every
 // window start.  One thread walks one kWin-byte window from its checkpoint, straight
@@ -2251,7 +2233,8 @@ __global__ void k_onepass_reset(uint64_t *st, uint32_t n, uint32_t *ctr) {
 // document whose useful map is empty, or that asks for a serial scan, is one lane.  Lanes
 // are numbered long single-lane documents first, so the longest walks start first; the
 // count workgroups take 64-lane tiles from an atomic queue (work stealing) after a first
-// tile fixed per wave, and the windowed emit gives each wave a contiguous range of tiles.
+// tile fixed per wave, and the windowed emit gives each workgroup a contiguous range of tiles, which
+// its waves claim in runs.
 // Each document's result is its own scan's: its tokens up to and including its first
 // halted slice, error offset relative to the document.
 //
@@ -3407,7 +3390,7 @@ __device__ __forceinline__ void batch_lane_emit(const BatchArgs &a, const BatchL
 
 // The windowed emit over a batch's documents.  Work items are tiles of 64 windows of one
 // document (windows: the kWin-aligned stretches of the address space, clipped to the
-// document), in contiguous ranges per wave; each wave walks one tile at a time, a window per thread,
+// document), in a contiguous range to a workgroup; each wave walks one tile at a time, a window per thread,
 // from the count walk's checkpoint, stages the tile's tokens and writes them out coalesced,
 // exactly as the single-buffer windowed emit does with the document as its input (its
 // slices, cut at certified bytes or at the hybrid plan's serial token starts, are the
