@@ -768,11 +768,12 @@ __device__ __forceinline__ uint32_t match16(const uint4 &v, const CertArg &ca, c
 // slice is walked again by `walk`, which falls back (FALL: the automaton may not be monotone).
 // At lim an accepting row counts its token.
 //
-// What bounds it: the chain of table lookups (about 73 CU cycles a step at one wave per SIMD)
-// until the LDS pipe is full (about 7 cycles a wave-step at 4 waves per SIMD, half of them bank
-// conflicts).  LINE: a lane's stretch is loaded in one go, so every 128-byte line is read once
-// when LINE is 128; with lanes of a few windows 64 wastes less at the slices' unaligned ends, and
-// the next stretch loads while one is walked.
+// What bounds it: the chain of table lookups, 73 to 76 CU cycles a step with the CU to itself; with
+// four waves per SIMD the LDS and the VALU together, about 14 CU cycles a wave-step (512 MiB in 2 KiB
+// lanes, 195 us: the LDS pipe busy 47% of the time, two thirds of that bank conflicts, the VALU 53%).
+// LINE: a lane's stretch is loaded in one go, so every 128-byte line is read once when LINE is 128;
+// with lanes of a few windows 64 wastes less at the slices' unaligned ends, and the next stretch
+// loads while one is walked.
 template <int LINE, bool CK, bool FALL>
 __device__ __forceinline__ bool walk_wave(LaneState &L, const Tables &tb, const uint8_t *in, uint32_t n, uint32_t s,
                                           uint32_t e, uint32_t lim, bool live, const CkSink &ck) {
@@ -1693,7 +1694,7 @@ __device__ __forceinline__ void win_walk(const Tables &tb, const WalkArgs &a, co
 // selects between this position and the token's start in one bitop3, positions relative to the
 // window, so that they are inline constants; and the next step's lookup, which the chain waits
 // for, issued ahead of this step's write (the LDS serves both in order).  9 VALU a byte instead
-// of 12 with discarded kinds, 7 instead of 9 without: the 256 MiB JSON scan 289 to 276 us.
+// of 12 with discarded kinds, 7 instead of 8 without: the 256 MiB JSON scan 289 to 276 us.
 template <bool DISC>
 __device__ __forceinline__ void win_walk_staged(const Tables &tb, const Win64 &d, uint32_t p0, uint32_t &st, WinOut &w) {
   uint32_t x = DISC ? w.tok - p0 : p0 - w.base;  // token start after the window's; window after P
@@ -2493,52 +2494,73 @@ __device__ __forceinline__ void group_prefix(const uint64_t *part, uint32_t q0, 
 }
 
 // Planning, first half: lanes per document, each group's lane, speculative-lane and tile
-// sums (v) and whether it holds a bad record; the queues reset.  The document table is the
+// sums (v) and whether it holds a bad record.  The document table is the
 // caller's device data: a document outside the bytes, an unknown instance or flag, or more
 // lanes than the workspace holds stops the batch.
 // v: single-lane long documents, other lanes, speculative lanes, tiles, bad; the first two in the
-// plan's lanes
-__device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[7],
+// plan's lanes (FINE: where the walked ones may be finer)
+template <bool FINE>
+__device__ __forceinline__ void plan_sums(const BatchArgs &a, uint32_t lo, uint32_t hi, uint64_t (&v)[FINE ? 7 : 5],
                                           uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.meta[kQCount] = 0;
-    a.meta[kQEmit] = 0;
-    a.meta[kAnyLane] = 0;
-  }
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
-  for (int q = 0; q < 7; ++q) v[q] = 0;
+  for (int q = 0; q < (FINE ? 7 : 5); ++q) v[q] = 0;
   for (uint32_t d = lo + threadIdx.x; d < hi; d += blockDim.x) {
     const DocDev x = a.docs[d];
     const bool fits = x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
     v[4] |= !fits || x.inst >= a.ninst || x.flags > 1;
-    const uint32_t nl = doc_lanes(a, rm, x, a.fine_bytes), np = doc_lanes(a, rm, x, a.lane_bytes);
+    const uint32_t nl = doc_lanes(a, rm, x, a.fine_bytes);
     a.spec_fail[d] = 0;
-    const bool first = nl == 1 && x.length > a.fine_bytes, firstp = np == 1 && x.length > a.lane_bytes;
+    const bool first = nl == 1 && x.length > a.fine_bytes;
     v[0] += first ? nl : 0;
     v[1] += first ? 0 : nl;
-    v[5] += firstp ? np : 0;
-    v[6] += firstp ? 0 : np;
+    if constexpr (FINE) {
+      const uint32_t np = doc_lanes(a, rm, x, a.lane_bytes);
+      const bool firstp = np == 1 && x.length > a.lane_bytes;
+      v[5] += firstp ? np : 0;
+      v[6] += firstp ? 0 : np;
+    }
     if (spec_split(a, rm, x)) v[2] += nl;
     if (fits) v[3] += doc_tiles(base + x.offset, x.length);
   }
-  block_sum<7>(v, red);
+  block_sum<FINE ? 7 : 5>(v, red);
+}
+
+// The batch's totals, queues and stop flags, by one thread.
+__device__ __forceinline__ void plan_meta(const BatchArgs &a, bool bad, uint64_t nlanes, uint64_t planned, uint64_t nspec,
+                                          uint64_t ntiles, bool fine) {
+  const bool stop = bad || planned > a.plan_lanes || nspec > a.max_spec;
+  a.meta[kQCount] = 0;
+  a.meta[kQEmit] = 0;
+  a.meta[kAnyLane] = 0;
+  a.meta[kFine] = fine ? a.fine_bytes : a.lane_bytes;
+  a.meta[kBad] = stop;
+  a.meta[kNLanes] = stop ? 0 : (uint32_t)nlanes;
+  a.meta[kNSpec] = stop ? 0 : (uint32_t)nspec;
+  // the windowed emit needs its checkpoints' rows in 8 bits and its tiles in the workspace
+  // (overlapping documents may ask for more tiles than the bytes hold)
+  const bool nowin = stop || !a.win_ok || ntiles > a.max_tiles;
+  a.meta[kNoWin] = nowin;
+  a.meta[kNTiles] = nowin ? 0 : (uint32_t)ntiles;
 }
 
 // Planning, second half: lane numbering (long single-lane documents first, then the rest,
 // each in document order), speculative-lane and tile numbering, from the sums of the earlier
 // groups (pre) and of all (tot); the first group writes the totals and the stop flags.
-__device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uint32_t hi, const uint64_t (&pre)[7],
-                                            const uint64_t (&tot)[7], uint64_t (*red)[kRedWaves]) {
+template <bool FINE>
+__device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uint32_t hi,
+                                            const uint64_t (&pre)[FINE ? 7 : 5],
+                                            const uint64_t (&tot)[FINE ? 7 : 5], uint64_t (*red)[kRedWaves]) {
   const uint32_t rm = refused_mask(a);
   const uintptr_t base = reinterpret_cast<uintptr_t>(a.bytes);
   // Beside split documents the count pass takes as long as their speculative walks, and finer lanes
   // only lengthen the document pass: 64 documents, one of 1.4 MB, 30 KB refused, 560 us in 128-byte
   // lanes, 436 in the plan's.
-  const bool fits_fine = tot[0] + tot[1] <= a.max_lanes && tot[2] == 0;
+  constexpr int kP = FINE ? 5 : 0;  // the plan's lanes' sums
+  const bool fits_fine = FINE && tot[0] + tot[1] <= a.max_lanes && tot[2] == 0;
   const uint32_t fine = fits_fine ? a.fine_bytes : a.lane_bytes;
   // 64-bit: a hostile table may ask for 2^32 lanes
-  uint64_t r[4] = {fits_fine ? pre[0] : pre[5], fits_fine ? tot[0] + pre[1] : tot[5] + pre[6], pre[2], pre[3]};
+  uint64_t r[4] = {fits_fine ? pre[0] : pre[kP], fits_fine ? tot[0] + pre[1] : tot[kP] + pre[kP + 1], pre[2], pre[3]};
   for (uint32_t d0 = lo; d0 < hi; d0 += blockDim.x) {  // workgroup-uniform: the scans see every thread
     const uint32_t d = d0 + threadIdx.x;
     const bool in = d < hi;
@@ -2562,17 +2584,8 @@ __device__ __forceinline__ void plan_number(const BatchArgs &a, uint32_t lo, uin
     for (int q = 0; q < 4; ++q) r[q] += t[q];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const uint64_t planned = tot[5] + tot[6], nlanes = fits_fine ? tot[0] + tot[1] : planned, nspec = tot[2];
-    const bool stop = tot[4] || planned > a.plan_lanes || nspec > a.max_spec;
-    a.meta[kFine] = fine;
-    a.meta[kBad] = stop;
-    a.meta[kNLanes] = stop ? 0 : (uint32_t)nlanes;
-    a.meta[kNSpec] = stop ? 0 : (uint32_t)nspec;
-    // the windowed emit needs its checkpoints' rows in 8 bits and its tiles in the workspace
-    // (overlapping documents may ask for more tiles than the bytes hold)
-    const bool nowin = stop || !a.win_ok || tot[3] > a.max_tiles;
-    a.meta[kNoWin] = nowin;
-    a.meta[kNTiles] = nowin ? 0 : (uint32_t)tot[3];
+    const uint64_t planned = tot[kP] + tot[kP + 1];
+    plan_meta(a, tot[4] != 0, fits_fine ? tot[0] + tot[1] : planned, planned, tot[2], tot[3], fits_fine);
   }
 }
 
@@ -2607,36 +2620,75 @@ __device__ __forceinline__ void map_docs(const BatchArgs &a, uint32_t wave, uint
   }
 }
 
+template <bool FINE>
 __global__ void __launch_bounds__(256) k_bplan_a(BatchArgs a) {
-  __shared__ uint64_t red[7][kRedWaves];
+  constexpr int Q = FINE ? 7 : 5;
+  __shared__ uint64_t red[Q][kRedWaves];
   uint32_t lo, hi;
   group_range(a.ndocs, lo, hi);
-  uint64_t v[7];
-  plan_sums(a, lo, hi, v, red);
-  if (threadIdx.x < 7) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
+  uint64_t v[Q];
+  plan_sums<FINE>(a, lo, hi, v, red);
+  if (threadIdx.x < Q) a.part[(size_t)blockIdx.x * kPartWords + threadIdx.x] = v[threadIdx.x];
 }
 
+template <bool FINE>
 __global__ void __launch_bounds__(256) k_bplan_b(BatchArgs a) {
-  __shared__ uint64_t red[14][kRedWaves];
-  uint64_t pre[7], tot[7];
-  group_prefix<7>(a.part, 0, pre, tot, red);
+  constexpr int Q = FINE ? 7 : 5;
+  __shared__ uint64_t red[2 * Q][kRedWaves];
+  uint64_t pre[Q], tot[Q];
+  group_prefix<Q>(a.part, 0, pre, tot, red);
   uint32_t lo, hi;
   group_range(a.ndocs, lo, hi);
-  plan_number(a, lo, hi, pre, tot, red);
+  plan_number<FINE>(a, lo, hi, pre, tot, red);
 }
 
 __global__ void __launch_bounds__(256) k_bmap(BatchArgs a) {
   map_docs(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
 }
 
-// A small batch (at most kOneDocs documents and kOneBytes bytes) in one launch of one workgroup:
-// a launch costs 4-5 us here, more than the planning of so few documents.
+// A small batch (at most kOneDocs documents and kOneBytes bytes) in one launch of one workgroup: a
+// launch costs 4-5 us here, more than the planning of so few documents.  A thread of the first wave
+// to a document; every sum fits 32 bits (a document longer than the bytes is bad and counts as
+// empty), so two share a scan, without the workgroup's barriers.
+constexpr uint32_t kOneDocs = 64;
+constexpr uint64_t kOneBytes = 4u << 20;
+static_assert(kOneDocs == 64, "one wave");
 __global__ void __launch_bounds__(1024) k_bplan_one(BatchArgs a) {
-  __shared__ uint64_t red[7][kRedWaves];
-  uint64_t tot[7];
-  const uint64_t pre[7] = {};
-  plan_sums(a, 0, a.ndocs, tot, red);
-  plan_number(a, 0, a.ndocs, pre, tot, red);
+  if (threadIdx.x < kOneDocs) {
+    const uint32_t rm = refused_mask(a), d = threadIdx.x;
+    const bool in = d < a.ndocs;
+    DocDev x{0, 0, 0, 0};
+    if (in) x = a.docs[d];
+    const bool fits = in && x.offset <= a.nbytes && x.length <= a.nbytes - x.offset;
+    const bool bad = __any(in && (!fits || x.inst >= a.ninst || x.flags > 1));
+    if (!fits) x.length = 0;
+    const uint32_t nf = in ? doc_lanes(a, rm, x, a.fine_bytes) : 0, np = in ? doc_lanes(a, rm, x, a.lane_bytes) : 0;
+    const bool ff = nf == 1 && x.length > a.fine_bytes, fp = np == 1 && x.length > a.lane_bytes;
+    auto pair = [](uint32_t lo, uint32_t hi) { return lo | (uint64_t)hi << 32; };
+    // lanes of long single-lane documents and others: walked, and the plan's; speculative lanes and tiles
+    const uint64_t v[3] = {pair(ff ? nf : 0, ff ? 0 : nf), pair(fp ? np : 0, fp ? 0 : np),
+                           pair(in && spec_split(a, rm, x) ? nf : 0,
+                                fits ? doc_tiles(reinterpret_cast<uintptr_t>(a.bytes) + x.offset, x.length) : 0)};
+    uint64_t pre[3], tot[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint64_t s = wave_incl64(v[q], d);
+      pre[q] = s - v[q];
+      tot[q] = __shfl(s, 63);
+    }
+    auto both = [](uint64_t s) { return (uint32_t)s + (uint32_t)(s >> 32); };
+    const bool fits_fine = both(tot[0]) <= a.max_lanes && (uint32_t)tot[2] == 0;  // as in plan_number
+    const int w = fits_fine ? 0 : 1;
+    if (in) {
+      const bool first = fits_fine ? ff : fp;
+      a.lanes_of[d] = fits_fine ? nf : np;
+      a.lane_base[d] = first ? (uint32_t)pre[w] : (uint32_t)tot[w] + (uint32_t)(pre[w] >> 32);
+      a.spec_base[d] = (uint32_t)pre[2];
+      a.tile_base[d] = (uint32_t)(pre[2] >> 32);
+      a.spec_fail[d] = 0;
+    }
+    if (d == 0) plan_meta(a, bad, both(tot[w]), both(tot[1]), (uint32_t)tot[2], tot[2] >> 32, fits_fine);
+  }
   __syncthreads();
   map_docs(a, threadIdx.x >> 6, blockDim.x >> 6);
 }
@@ -3219,13 +3271,14 @@ __device__ __forceinline__ bool doc_pass(const BatchArgs &a, uint32_t d, uint32_
   return nowin;
 }
 
-// A wave per document.  True if some document of this wave's takes the lane emit.  FINE: lanes finer
-// than the plan's may be walked (without them fewer registers, more documents at a time).
+// A wave per document.  True if some document of this wave's takes the lane emit.  R: the walked lanes
+// per plan lane that may occur: 1 alone (fewer registers, more documents at a time), 1 or 8 (less
+// code), or any (0).
 constexpr uint32_t kLongDoc = 512;  // walked lanes from which a thread takes a plan lane's (eight steps against one)
-template <bool FINE>
+template <int R>
 __device__ __forceinline__ bool doc_passes(const BatchArgs &a, uint32_t wave, uint32_t nwaves) {
   const uint32_t rm = refused_mask(a), fine = a.meta[kFine];
-  const uint32_t ratio = FINE ? a.lane_bytes / fine : 1;  // 1, 2, 4 or 8; 1 beside split documents
+  const uint32_t ratio = R == 1 ? 1 : a.lane_bytes / fine;  // 1, 2, 4 or 8; 1 beside split documents
   bool any_lane = false;
   // the next document's lane range loads while the current one is scanned
   uint32_t n_lb = 0, n_nl = 1;
@@ -3241,11 +3294,11 @@ __device__ __forceinline__ bool doc_passes(const BatchArgs &a, uint32_t wave, ui
     }
     const DocDev doc = a.docs[d];
     const uint32_t lane_bytes = spec_split(a, rm, doc) ? a.spec_bytes : fine;
-    const uint32_t k = !FINE || nl < kLongDoc ? 1 : ratio;  // wave-uniform
-    any_lane |= k == 8   ? doc_pass<8>(a, d, lb, nl, doc, lane_bytes, 1)
-                : k == 4 ? doc_pass<4>(a, d, lb, nl, doc, lane_bytes, 1)
-                : k == 2 ? doc_pass<2>(a, d, lb, nl, doc, lane_bytes, 1)
-                         : doc_pass<1>(a, d, lb, nl, doc, lane_bytes, ratio);
+    const uint32_t k = R == 1 || nl < kLongDoc ? 1 : ratio;  // wave-uniform
+    any_lane |= R != 1 && k == 8   ? doc_pass<8>(a, d, lb, nl, doc, lane_bytes, 1)
+                : R == 0 && k == 4 ? doc_pass<4>(a, d, lb, nl, doc, lane_bytes, 1)
+                : R == 0 && k == 2 ? doc_pass<2>(a, d, lb, nl, doc, lane_bytes, 1)
+                                   : doc_pass<1>(a, d, lb, nl, doc, lane_bytes, ratio);
   }
   return any_lane;
 }
@@ -3304,10 +3357,10 @@ __device__ __forceinline__ void result_bad(const BatchArgs &a) {
   }
 }
 
-template <bool FINE>
+template <int R>
 __global__ void __launch_bounds__(256) k_bdoc(BatchArgs a) {
   if (a.meta[kBad]) return;
-  const bool any = doc_passes<FINE>(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+  const bool any = doc_passes<R>(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
   if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;  // every writer stores the same value
 }
 
@@ -3337,7 +3390,7 @@ __global__ void __launch_bounds__(256) k_bscan_b(BatchArgs a) {
 __global__ void __launch_bounds__(1024) k_bdoc_one(BatchArgs a) {
   __shared__ uint64_t red[3][kRedWaves];
   if (a.meta[kBad]) return result_bad(a);
-  const bool any = doc_passes<true>(a, threadIdx.x >> 6, blockDim.x >> 6);
+  const bool any = doc_passes<8>(a, threadIdx.x >> 6, blockDim.x >> 6);
   if ((threadIdx.x & 63) == 0 && any) a.meta[kAnyLane] = 1;
   __syncthreads();
   uint64_t tot[3];
@@ -4059,8 +4112,7 @@ static WalkArgs walk_args(const DevTable &t, const CertMap &cm, const uint8_t *i
 // refused set, one lane: 105 us in 128-byte stretches, 99 so; path 1 on 3 KB 54 and 46).
 constexpr uint32_t kShortLane = 512, kShortLaneOne = 1024, kFewLanes = 64u << 10;
 // Batches: the shortest walked lane; what one workgroup plans and reports.
-constexpr uint32_t kFineLane = 128, kOneDocs = 64, kMaxRatio = 8;
-constexpr uint64_t kOneBytes = 4u << 20;
+constexpr uint32_t kFineLane = 128, kMaxRatio = 8;
 
 static inline void mark(hipEvent_t const *ev, int i, hipStream_t s) {
   if (ev && ev[i]) (void)hipEventRecord(ev[i], s);
@@ -4317,6 +4369,7 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
   const uint32_t ngroups = doc_groups(ndocs);
   // A small batch plans and reports in one workgroup each (k_bplan_one, k_bdoc_one): up to
   // kOneDocs documents, and few enough lanes and tiles for one workgroup to number and sum.
+  // (A default lane of so few bytes is walked in eighths: kFineLane.)
   const bool one = ndocs <= kOneDocs && nbytes <= kOneBytes;
   bool refused = false;  // some instance takes the hybrid plan
   for (uint32_t k = 0; k < bt.ninst; ++k) refused = refused || bt.inst[k].refused;
@@ -4327,9 +4380,11 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
     k_bplan_one<<<1, 1024, 0, s>>>(a);
     if (!launched()) return e;
   } else {
-    k_bplan_a<<<ngroups, 256, 0, s>>>(a);
+    if (a.fine_bytes < a.lane_bytes) k_bplan_a<true><<<ngroups, 256, 0, s>>>(a);
+    else k_bplan_a<false><<<ngroups, 256, 0, s>>>(a);
     if (!launched()) return e;
-    k_bplan_b<<<ngroups, 256, 0, s>>>(a);
+    if (a.fine_bytes < a.lane_bytes) k_bplan_b<true><<<ngroups, 256, 0, s>>>(a);
+    else k_bplan_b<false><<<ngroups, 256, 0, s>>>(a);
     if (!launched()) return e;
     k_bmap<<<gdoc, 256, 0, s>>>(a);
     if (!launched()) return e;
@@ -4355,8 +4410,9 @@ hipError_t run_batch(const BatchTables &bt, const uint8_t *bytes, uint64_t nbyte
     k_bdoc_one<<<1, 1024, 0, s>>>(a);
     if (!launched()) return e;
   } else {
-    if (a.fine_bytes < a.lane_bytes) k_bdoc<true><<<gdoc, 256, 0, s>>>(a);
-    else k_bdoc<false><<<gdoc, 256, 0, s>>>(a);
+    if (a.fine_bytes == a.lane_bytes) k_bdoc<1><<<gdoc, 256, 0, s>>>(a);
+    else if (a.fine_bytes * 8 == a.lane_bytes) k_bdoc<8><<<gdoc, 256, 0, s>>>(a);
+    else k_bdoc<0><<<gdoc, 256, 0, s>>>(a);
     if (!launched()) return e;
     k_bscan_a<<<ngroups, 256, 0, s>>>(a);
     if (!launched()) return e;
