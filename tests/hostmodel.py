@@ -159,7 +159,7 @@ def windowed(model, w: bytes, starts, ends, lane: int, base: int, block: int = 4
 
     starts/ends: the lanes' slices (lane j nominally covers [j l, (j+1) l)).  base: the
     input's address modulo W.  block: lanes per count workgroup.  Returns (kinds, lens, offs),
-    or None when a slice halts (the library then uses the lane emit).  Mirrors the kernels'
+    or None when a slice halts (the library emits up to the halt; not modelled).  Mirrors the kernels'
     bookkeeping: window checkpoints, owner lookup through the last-non-empty-lane prefixes,
     64-window tiles, the staged words (end - P) << 8 | kind after 4 to 7 padding slots (in a
     mode with discarded kinds, length << 8 | kind, and no staging when offsets are asked
